@@ -38,10 +38,18 @@ hipError_t launch_smooth_step(const OpDesc<TC>& op, const T* x, const T* xprev, 
 // fused row kernel does not apply and `scratch` (n^3 elements, distinct from
 // x, b and coarse) is given, the residual is formed there first and then
 // restricted (two passes); without scratch a fused gather kernel is used.
+// first (19-point, two-pass form): the restriction also writes the coarse
+// level's first smoothing step from zero, first.x1 = first.c0 coarse / D.
+template <typename T>
+struct FirstStep {
+    const T* C = nullptr;  // coarse coefficients
+    T* x1 = nullptr;       // nullptr: not wanted
+    double c0 = 0.0;
+};
 template <typename T, typename TC>
 hipError_t launch_residual_restrict(const OpDesc<TC>& op, const T* x, const T* b, T* coarse,
                                     T* scratch, hipStream_t s, hipEvent_t ev0 = nullptr,
-                                    hipEvent_t ev1 = nullptr);
+                                    hipEvent_t ev1 = nullptr, const FirstStep<T>& first = FirstStep<T>());
 
 // coarse = R(fine), componentwise for `ncomp` consecutive fields.
 template <typename T>

@@ -20,6 +20,8 @@
 #include "kernels.h"
 #include "tail.h"
 #include "var_row.h"
+#include "var_tail.h"
+#include "var_visit.h"
 #include "visit.h"
 
 #include <type_traits>
@@ -37,6 +39,7 @@ struct Level {
     void* coeff = nullptr;            // inner-precision coefficients (6 N), nullptr for 7-point
     double lmax = 2.0;                // Gershgorin bound of D^-1 M
     int cur = 0;                      // which x holds the current iterate
+    bool x1 = false;                  // x[0] already holds the first step from zero for the current b
     // smoothing schedule: step k computes x + a_k (x - x_prev) + c_k D^-1 (b - M x)
     std::vector<double> a, c;
 };
@@ -338,6 +341,20 @@ inline bool visit_level(const mg_ctx* c, int l, bool pre) {
     return pre ? visit_pre_applies(n, v) : visit_post_applies(n, v);
 }
 
+// 19-point levels of 32^3 points: pre- and post-visits in one launch each.
+inline bool var_visit_level(const mg_ctx* c, int l) {
+    return c->use_visits && c->var && l + 1 < (int)c->lev.size() && l != c->tail_start &&
+           var_visit_applies(c->lev[l].n, (int)c->lev[l].a.size(),
+                             c->inner_double ? sizeof(double) : sizeof(float));
+}
+
+// Level l's pass from zero can start from a first step written by the
+// restriction that produces its right-hand side (19-point levels smoothed by
+// separate kernels or visits).
+inline bool first_step_level(const mg_ctx* c, int l) {
+    return c->var && l > 0 && l + 1 < (int)c->lev.size() && l != c->tail_start;
+}
+
 // Level l's post-smoothing pass (three Chebyshev steps) runs fused with the
 // prolongation before it.
 inline bool post_fused(const mg_ctx* c, int l, size_t elem) {
@@ -407,6 +424,12 @@ mg_status smooth_level(mg_ctx* c, int l, bool from_zero, const T* pro_e = nullpt
         if (k == 0 && from_zero && l == 0 && c->x1_ready) {  // formed by the outer residual kernel
             c->x1_ready = false;
             cur = c->x1_buf;
+            prev = -1;
+            continue;
+        }
+        if (k == 0 && from_zero && L.x1) {  // formed by the restriction above
+            L.x1 = false;
+            cur = 0;
             prev = -1;
             continue;
         }
@@ -589,8 +612,34 @@ mg_status coarse_level(mg_ctx* c, int l) {
     return MG_OK;
 }
 
+// The variable-coefficient levels from l0 down in one workgroup.
+template <typename T>
+mg_status var_tail_cycle(mg_ctx* c, int l0) {
+    VarTailArgs<T> a{};
+    a.nlev = (int)c->lev.size() - l0;
+    a.sched.cheb = c->p.smoother == MG_CHEBYSHEV ? 1 : 0;
+    a.sched.steps = (int)c->lev[l0].a.size();
+    for (int k = 0; k < a.nlev; ++k) {
+        const Level& Lv = c->lev[l0 + k];
+        a.n[k] = Lv.n;
+        a.ih2[k] = Lv.ih2;
+        a.C[k] = (const T*)Lv.coeff;
+        for (int j = 0; j < a.sched.steps; ++j) {
+            a.sched.a[k][j] = Lv.a[j];
+            a.sched.c[k][j] = Lv.c[j];
+        }
+    }
+    a.b = (const T*)c->lev[l0].b;
+    a.x = (T*)c->lev[l0].x[0];
+    a.G = c->G;
+    HIPCHK(c, launch_var_tail<T>(a, c->stream));
+    c->lev[l0].cur = 0;
+    return MG_OK;
+}
+
 template <typename T>
 mg_status tail_cycle(mg_ctx* c, int l0) {
+    if (c->var) return var_tail_cycle<T>(c, l0);
     TailArgs<T> a{};
     const int L = (int)c->lev.size();
     a.nlev = L - l0;
@@ -624,17 +673,25 @@ template <typename T>
 mg_status vcycle_from_zero(mg_ctx* c, int l);
 
 // r_{l+1} = R(b_l - M_l x_l) into level l+1's right-hand side; the buffer of
-// the previous iterate is free here and serves as residual scratch.
+// the previous iterate is free here and serves as residual scratch.  cycle: a
+// V-cycle on level l + 1 follows, whose first step may be formed here.
 template <typename T>
-mg_status residual_restrict_level(mg_ctx* c, int l) {
+mg_status residual_restrict_level(mg_ctx* c, int l, bool cycle = false) {
     Level& L = c->lev[l];
     Level& Lc = c->lev[l + 1];
     const bool fine = (l == 0);
     hipEvent_t ev0, ev1;
     mg_status st = time_events(c, fine, MG_TIME_TRANSFER, &ev0, &ev1);
     if (st != MG_OK) return st;
+    FirstStep<T> first;
+    if (cycle && first_step_level(c, l + 1)) {
+        first.C = (const T*)Lc.coeff;
+        first.x1 = (T*)Lc.x[0];
+        first.c0 = Lc.c[0];
+        Lc.x1 = true;
+    }
     HIPCHK(c, launch_residual_restrict<T, T>(op_of<T>(L), (const T*)L.x[L.cur], (const T*)L.b, (T*)Lc.b,
-                                             (T*)L.x[other(L.cur)], c->stream, ev0, ev1));
+                                             (T*)L.x[other(L.cur)], c->stream, ev0, ev1, first));
     // seven-point: x, b read, r_{l+1} written; 19-point: the timed pass forms
     // the fine residual (x, b, C read, r written) and a second pass restricts it
     const double N = (double)L.N, s = sizeof(T);
@@ -671,6 +728,43 @@ mg_status post_level(mg_ctx* c, int l) {
     return smooth_level<T>(c, l, false);
 }
 
+// The first step from zero of a 19-point visit level, where the kernel that
+// wrote the right-hand side did not form it.
+template <typename T>
+mg_status ensure_first_step(mg_ctx* c, int l) {
+    Level& L = c->lev[l];
+    if (L.x1) return MG_OK;
+    HIPCHK(c, launch_smooth_step<T, T>(op_of<T>(L), nullptr, nullptr, (const T*)L.b, (T*)L.x[0], 0.0, L.c[0],
+                                       c->stream));
+    L.x1 = true;
+    return MG_OK;
+}
+
+// Down-leg of a 19-point visit level.
+template <typename T>
+mg_status var_visit_pre(mg_ctx* c, int l) {
+    Level& L = c->lev[l];
+    Level& Lc = c->lev[l + 1];
+    int in = 0;
+    if (l == 0 && c->x1_ready) {
+        in = c->x1_buf;
+        c->x1_ready = false;
+    } else {
+        const mg_status st = ensure_first_step<T>(c, l);
+        if (st != MG_OK) return st;
+    }
+    L.x1 = false;
+    const bool first = first_step_level(c, l + 1);
+    const int out = other(in);
+    HIPCHK(c, launch_var_visit_pre<T>(L.n, L.ih2, (const T*)L.coeff, (const T*)L.x[in], (const T*)L.b, (T*)L.x[out],
+                                      (T*)Lc.b, (const T*)Lc.coeff, first ? (T*)Lc.x[0] : nullptr,
+                                      Lc.c.empty() ? 0.0 : Lc.c[0], L.a.data(), L.c.data(), (int)L.a.size(),
+                                      c->p.smoother == MG_CHEBYSHEV, c->stream));
+    Lc.x1 = first;
+    L.cur = out;
+    return MG_OK;
+}
+
 // Capture V(0, b_1) on level 1 and below into c->coarse_exec.
 template <typename T>
 mg_status capture_coarse(mg_ctx* c) {
@@ -700,12 +794,17 @@ template <typename T>
 mg_status vcycle_from_zero(mg_ctx* c, int l) {
     const int last = (int)c->lev.size() - 1;
     if (l == 1 && last >= 2 && c->use_graph && !c->capturing) {
+        if (first_step_level(c, 1)) {  // the captured cycle starts from the first step
+            mg_status st = ensure_first_step<T>(c, 1);
+            if (st != MG_OK) return st;
+        }
         if (!c->coarse_exec) {
             mg_status st = capture_coarse<T>(c);
             if (st != MG_OK) return st;
         }
         HIPCHK(c, hipGraphLaunch(c->coarse_exec, c->stream));
         c->lev[1].cur = c->coarse_cur;
+        c->lev[1].x1 = false;
         return MG_OK;
     }
     if (l == c->tail_start) return tail_cycle<T>(c, l);
@@ -719,15 +818,25 @@ mg_status vcycle_from_zero(mg_ctx* c, int l) {
         HIPCHK(c, launch_visit_pre(L.n, L.ih2, (const float*)L.b, (float*)L.x[0], (float*)Lc.b, L.a.data(),
                                    L.c.data(), v, c->stream));
         L.cur = 0;
+    } else if (var_visit_level(c, l)) {
+        if ((st = var_visit_pre<T>(c, l)) != MG_OK) return st;
     } else {
         if ((st = smooth_level<T>(c, l, true)) != MG_OK) return st;
-        if ((st = residual_restrict_level<T>(c, l)) != MG_OK) return st;
+        if ((st = residual_restrict_level<T>(c, l, true)) != MG_OK) return st;
     }
     if ((st = vcycle_from_zero<T>(c, l + 1)) != MG_OK) return st;
     if (std::is_same<T, float>::value && visit_level(c, l, false)) {  // and one after it
         const int nx = other(L.cur);
         HIPCHK(c, launch_visit_post(L.n, L.ih2, (const float*)L.x[L.cur], (const float*)Lc.x[Lc.cur],
                                     (const float*)L.b, (float*)L.x[nx], L.a.data(), L.c.data(), v, c->stream));
+        L.cur = nx;
+        return MG_OK;
+    }
+    if (var_visit_level(c, l)) {
+        const int nx = other(L.cur);
+        HIPCHK(c, launch_var_visit_post<T>(L.n, L.ih2, (const T*)L.coeff, (const T*)L.x[L.cur],
+                                           (const T*)Lc.x[Lc.cur], (const T*)L.b, (T*)L.x[nx], L.a.data(),
+                                           L.c.data(), v, c->p.smoother == MG_CHEBYSHEV, c->stream));
         L.cur = nx;
         return MG_OK;
     }
@@ -1060,6 +1169,13 @@ static mg_status create_impl(mg_ctx* c, const void* coeff, int coeff_dtype, cons
         }
         HIPCHK(c, hipStreamSynchronize(c->stream));
         free64();
+        // levels of at most 16^3 points run in one kernel (coarsest 8^3 or 4^3)
+        const int steps = p.smoother == MG_JACOBI ? p.jacobi_sweeps : p.cheb_degree;
+        if (c->use_tail && steps <= kTailMaxSteps) {
+            int l0 = p.levels - 1;
+            while (l0 > 0 && c->lev[l0 - 1].n <= 16) --l0;
+            if (var_tail_applies(c->lev[l0].n, c->lev.back().n, p.levels - l0)) c->tail_start = l0;
+        }
     } else {
         Level& Lc = c->lev.back();
         std::vector<double> Q, lam;
@@ -1684,6 +1800,7 @@ mg_status inner_step_impl(mg_ctx* c, int step, int l, const double* x, const dou
     Level* Lc = l + 1 < (int)c->lev.size() ? &c->lev[l + 1] : nullptr;
     hipStream_t s = c->stream;
     c->x1_ready = false;
+    for (Level& Lv : c->lev) Lv.x1 = false;
     c->pending_sums = false;
     auto in = [&](size_t count, const double* src, void* dst) -> hipError_t {
         return launch_convert<T, double>(count, src, (T*)dst, s);
