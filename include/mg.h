@@ -169,8 +169,9 @@ mg_status mg_vcycle(mg_ctx* ctx, double* phi, const double* b, double* rel_res_o
  * The loop also stops when the residual has failed to decrease by 0.1% over
  * two consecutive cycles (stagnation at the rounding floor of the precision).
  * info may be NULL.  Returns MG_ERR_NOT_CONVERGED (phi still valid) when the
- * tolerance is not reached, MG_ERR_NONFINITE on NaN/Inf.  Synchronises the
- * stream once per cycle (one 8-byte norm read back). */
+ * tolerance is not reached, MG_ERR_NONFINITE on NaN/Inf.  Waits for one norm
+ * read back per cycle (while the next cycle runs) and synchronises the stream
+ * at the end. */
 mg_status mg_solve(mg_ctx* ctx, double* phi, const double* b, double tol,
                    int max_cycles, mg_solve_info* info);
 
@@ -183,8 +184,8 @@ mg_status mg_solve(mg_ctx* ctx, double* phi, const double* b, double tol,
  * phi (gauge) as mg_solve does.  cycles >= 0 (0 only evaluates the residual
  * and gauge-fixes).  rel_res_out (host pointer, may be NULL) receives
  * ||b - M phi|| / ||b|| of the returned phi (0 if b is zero after
- * projection, in which case phi = 0).  Synchronises the stream twice: for
- * the mean of b at the start and for the final norms at the end.  Errors:
+ * projection, in which case phi = 0).  Waits for the mean of b while the
+ * first cycle runs and synchronises the stream once, at the end.  Errors:
  * MG_ERR_INVALID, MG_ERR_NONFINITE (NaN/Inf in b or in the final residual),
  * MG_ERR_HIP. */
 mg_status mg_cycles(mg_ctx* ctx, double* phi, const double* b, int cycles, double* rel_res_out);

@@ -75,7 +75,7 @@ hipError_t launch_smooth_pair_row(int n, double ih2, const T* x, const T* xp, co
                                   double cd0 = 0.0, const SumsJob* sums = nullptr, const T* ec = nullptr);
 template <typename TA, typename TR, typename TE>
 hipError_t launch_outer_row(int n, double ih2, const double* phi_in, const TE* e, double* phi_out, const double* b,
-                            double bmean, TR* r, TR* x1, double cd0, double* partials, hipStream_t s,
+                            Mean bmean, TR* r, TR* x1, double cd0, double* partials, hipStream_t s,
                             hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 template <typename T>
 hipError_t launch_rr_row(int n, double ih2, const T* x, const T* b, T* coarse, hipStream_t s,

@@ -432,9 +432,10 @@ __device__ __forceinline__ TA ld_value1(const double* phi, const TE* e, size_t i
 template <typename TA, typename TR, typename TE, int VEC, bool UPDATE, int S = 1>
 __global__ __launch_bounds__(kBlock) void k_outer_row(int n, TA ih2, const double* __restrict__ phi_in,
                                                       const TE* __restrict__ e, double* __restrict__ phi_out,
-                                                      const double* __restrict__ b, double bmean,
+                                                      const double* __restrict__ b, Mean bm,
                                                       TR* __restrict__ r, TR* __restrict__ x1, TA cd0,
                                                       double* __restrict__ partials, int nz, int nyb) {
+    const double bmean = bm.get();
     static_assert(kWaves % S == 0, "a block holds whole rows");
     __shared__ double sh[3 * kWaves];
     constexpr int NR = 64 * VEC;
@@ -1329,9 +1330,10 @@ __global__ __launch_bounds__(64 * NW) void k_smooth3p_lds(int n, T ih2, const T*
 template <typename TA, typename TR, typename TE, int VEC, int W, bool UPDATE, int S = 1>
 __global__ __launch_bounds__(64 * W * S) void k_outer_lds(int n, TA ih2, const double* __restrict__ phi_in,
                                                           const TE* __restrict__ e, double* __restrict__ phi_out,
-                                                          const double* __restrict__ b, double bmean,
+                                                          const double* __restrict__ b, Mean bm,
                                                           TR* __restrict__ r, TR* __restrict__ x1, TA cd0,
                                                           double* __restrict__ partials, int nz, int nyb) {
+    const double bmean = bm.get();
     constexpr int NR = 64 * VEC, NF = NR * S;
     __shared__ TA rows[2][W + 2][NF];
     __shared__ double sh[3 * W * S];
@@ -1814,11 +1816,13 @@ constexpr int kRrTarget = 512;
 // Longest z chunks that still give one block of kLdsWaves waves per CU: the
 // outer kernel is bound by its bytes, and a chunk re-reads its two halo planes
 // (256^3: chunks of 32 planes 103.6 us against 107.8 us for 16; 16-wave
-// blocks measured slower).
+// blocks measured slower).  Down to 4 planes where the level is small: with
+// at least 16 the 64^3 level ran 32 blocks and the 128^3 level 128 (64^3
+// double 15.4 -> 6.9 us, 128^3 float 20.2 -> 15.5 us a launch).
 void outer_lds_shape(int n, int waves, int& nz, int& nyb, int& blocks) {
     nyb = n / waves;
     nz = n;
-    while (nz > 16 && nyb * (n / nz) < 256) nz >>= 1;
+    while (nz > 4 && nyb * (n / nz) < 256) nz >>= 1;
     blocks = nyb * (n / nz);
 }
 
@@ -2362,7 +2366,7 @@ template hipError_t launch_smooth_triple_row<double>(int, double, const double*,
 
 template <typename TA, typename TR, typename TE>
 hipError_t launch_outer_row(int n, double ih2, const double* phi_in, const TE* e, double* phi_out, const double* b,
-                            double bmean, TR* r, TR* x1, double cd0, double* partials, hipStream_t s,
+                            Mean bmean, TR* r, TR* x1, double cd0, double* partials, hipStream_t s,
                             hipEvent_t ev0, hipEvent_t ev1) {
     int nz, nyb, blocks;
     if (outer_seg_lds(n, sizeof(TA))) {
@@ -2560,13 +2564,13 @@ template hipError_t launch_rr_row<double>(int, double, const double*, const doub
 template hipError_t launch_prolong_row<float>(int, const float*, float*, hipStream_t, hipEvent_t, hipEvent_t);
 template hipError_t launch_prolong_row<double>(int, const double*, double*, hipStream_t, hipEvent_t, hipEvent_t);
 template hipError_t launch_outer_row<double, double, double>(int, double, const double*, const double*, double*,
-                                                             const double*, double, double*, double*, double,
+                                                             const double*, Mean, double*, double*, double,
                                                              double*, hipStream_t, hipEvent_t, hipEvent_t);
 template hipError_t launch_outer_row<double, float, float>(int, double, const double*, const float*, double*,
-                                                           const double*, double, float*, float*, double, double*,
+                                                           const double*, Mean, float*, float*, double, double*,
                                                            hipStream_t, hipEvent_t, hipEvent_t);
 template hipError_t launch_outer_row<float, float, float>(int, double, const double*, const float*, double*,
-                                                          const double*, double, float*, float*, double, double*,
+                                                          const double*, Mean, float*, float*, double, double*,
                                                           hipStream_t, hipEvent_t, hipEvent_t);
 
 }  // namespace mg

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <cstddef>
 
+#include "sums.h"
+
 namespace mg {
 
 // Operator of one level: constant-coefficient seven-point Laplacian when
@@ -76,7 +78,7 @@ hipError_t launch_apply(const OpDesc<TC>& op, const T* u, T* out, hipStream_t s)
 // (phi_out when e != nullptr, else phi_in), all in double.
 template <typename TA, typename TR, typename TE, typename TC>
 hipError_t launch_outer_residual(const OpDesc<TC>& op, const double* phi_in, const TE* e,
-                                 double* phi_out, const double* b, double bmean, TR* r,
+                                 double* phi_out, const double* b, Mean bmean, TR* r,
                                  TR* x1, double c0, double* partials, hipStream_t s,
                                  hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
@@ -85,13 +87,14 @@ hipError_t launch_outer_residual(const OpDesc<TC>& op, const double* phi_in, con
 hipError_t launch_block_sums(int n, const double* u, double shift, int p, double* partials,
                              hipStream_t s);
 // out[slot + k] = sum_{i < count} partials[k * count + i], k < arrays (one block);
-// also into host_out[slot + k] (pinned host memory, visible to the host once an
-// event recorded after the launch has completed) when host_out is not null.
+// also into host_out[slot + k] (pinned host memory) when host_out is not null,
+// visible to the host once host_out[kHostFlagSlot] holds seq (seq != 0).
 hipError_t launch_finalize_sums(const double* partials, int count, int arrays, double* out, int slot,
-                                hipStream_t s, double* host_out = nullptr);
-// out[slot] = sum_{i < count} partials[i] in a fixed order (one block).
+                                hipStream_t s, double* host_out = nullptr, double seq = 0.0);
+// out[slot] = sum_{i < count} partials[i] in a fixed order (one block); with
+// host_out also host_out[slot], then seq into host_out[kHostMeanSlot].
 hipError_t launch_finalize_sum(const double* partials, int count, double* out, int slot,
-                               hipStream_t s);
+                               hipStream_t s, double* host_out = nullptr, double seq = 0.0);
 // out[slot] = max_{i < count} partials[i].
 hipError_t launch_finalize_max(const double* partials, int count, double* out, int slot,
                                hipStream_t s);
@@ -99,6 +102,9 @@ hipError_t launch_finalize_max(const double* partials, int count, double* out, i
 // ---- elementwise -----------------------------------------------------------------
 // dst = src - shift (double, may alias)
 hipError_t launch_shift(size_t count, const double* src, double shift, double* dst, hipStream_t s);
+// dst = src - sums[3] * inv, or 0 where sums[1] == 0 (device sums of an outer
+// residual: [1] of (b - mean)^2, [3] of the potential); may alias
+hipError_t launch_gauge(size_t count, const double* src, const double* sums, double inv, double* dst, hipStream_t s);
 // dst = src + e (double += T)
 template <typename T>
 hipError_t launch_add(size_t count, const double* src, const T* e, double* dst, hipStream_t s);

@@ -187,9 +187,10 @@ __global__ __launch_bounds__(kThreads) void k_outer_residual(int n, TA ih2, cons
                                                              const double* __restrict__ phi_in,
                                                              const TE* __restrict__ e,
                                                              double* __restrict__ phi_out,
-                                                             const double* __restrict__ b, double bmean,
+                                                             const double* __restrict__ b, Mean bm,
                                                              TR* __restrict__ r, TR* __restrict__ x1, TA c0,
                                                              double* partials, int nz) {
+    const double bmean = bm.get();
     __shared__ double sh[kThreads];
     const Grid g{n, n - 1};
     const size_t N = (size_t)n * n * n;
@@ -260,13 +261,21 @@ __global__ __launch_bounds__(kThreads) void k_block_sums(int n, const double* __
 }
 
 __global__ __launch_bounds__(1024) void k_finalize(const double* __restrict__ partials, int count, double* out,
-                                                   int slot, int is_max) {
+                                                   int slot, int is_max, double* host_out, double seq) {
     __shared__ double sh[1024];
     const int tid = threadIdx.x;
     double v = is_max ? -INFINITY : 0.0;
     for (int i = tid; i < count; i += 1024) v = is_max ? fmax(v, partials[i]) : v + partials[i];
     const double r = is_max ? block_max(v, sh) : block_sum(v, sh);
-    if (tid == 0) out[slot] = r;
+    if (tid == 0) {
+        out[slot] = r;
+        if (host_out) {  // pinned host mirror, then the flag the host polls
+            host_out[slot] = r;
+            __threadfence_system();
+            *reinterpret_cast<volatile double*>(host_out + kHostMeanSlot) = seq;
+            __threadfence_system();
+        }
+    }
 }
 
 // out[slot + k] = sum of partials[k * count .. (k + 1) * count), k < arrays
@@ -282,6 +291,25 @@ __global__ __launch_bounds__(kSumLanes) void k_finalize_multi(SumsJob job) {
 __global__ void k_shift(size_t count, const double* src, double shift, double* dst) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
         dst[i] = src[i] - shift;
+}
+// dst = src - mean(src), or zero where the source norm (sums[1]) is zero; the
+// sum of src is sums[3]
+__global__ __launch_bounds__(kThreads) void k_gauge(size_t pairs, const double2* src, const double* sums, double inv,
+                                                    double2* dst) {
+    const bool zero = sums[1] == 0.0;
+    const double shift = sums[3] * inv;
+    // four pairs in flight per thread: 8 us at 128^3 where one value per thread took 17.5
+    const size_t stride = (size_t)gridDim.x * kThreads;
+    for (size_t i = blockIdx.x * (size_t)kThreads + threadIdx.x; i < pairs; i += 4 * stride) {
+        double2 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (i + k * stride < pairs) v[k] = src[i + k * stride];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (i + k * stride < pairs)
+                dst[i + k * stride] = zero ? make_double2(0.0, 0.0) : make_double2(v[k].x - shift, v[k].y - shift);
+    }
 }
 template <typename T>
 __global__ void k_add(size_t count, const double* src, const T* e, double* dst) {
@@ -727,7 +755,7 @@ hipError_t launch_apply(const OpDesc<TC>& op, const T* u, T* out, hipStream_t s)
 
 template <typename TA, typename TR, typename TE, typename TC>
 hipError_t launch_outer_residual(const OpDesc<TC>& op, const double* phi_in, const TE* e, double* phi_out,
-                                 const double* b, double bmean, TR* r, TR* x1, double c0, double* partials,
+                                 const double* b, Mean bmean, TR* r, TR* x1, double c0, double* partials,
                                  hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     if (op.coeff == nullptr && row_kernels_apply(op.n))
         return launch_outer_row<TA, TR, TE>(op.n, op.ih2, phi_in, e, phi_out, b, bmean, r, x1,
@@ -751,23 +779,31 @@ hipError_t launch_block_sums(int n, const double* u, double shift, int p, double
     hipLaunchKernelGGL(k_block_sums, sh.grid, sh.block, 0, s, n, u, shift, p, partials, sh.nz);
     return hipGetLastError();
 }
-hipError_t launch_finalize_sum(const double* partials, int count, double* out, int slot, hipStream_t s) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, partials, count, out, slot, 0);
+hipError_t launch_finalize_sum(const double* partials, int count, double* out, int slot, hipStream_t s,
+                               double* host_out, double seq) {
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, partials, count, out, slot, 0, host_out, seq);
     return hipGetLastError();
 }
 hipError_t launch_finalize_sums(const double* partials, int count, int arrays, double* out, int slot,
-                                hipStream_t s, double* host_out) {
-    const SumsJob job{partials, count, arrays, out, slot, host_out};
+                                hipStream_t s, double* host_out, double seq) {
+    const SumsJob job{partials, count, arrays, out, slot, host_out, seq};
     hipLaunchKernelGGL(k_finalize_multi, dim3(1), dim3(kSumLanes), 0, s, job);
     return hipGetLastError();
 }
 hipError_t launch_finalize_max(const double* partials, int count, double* out, int slot, hipStream_t s) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, partials, count, out, slot, 1);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, partials, count, out, slot, 1, (double*)nullptr, 0.0);
     return hipGetLastError();
 }
 
 hipError_t launch_shift(size_t count, const double* src, double shift, double* dst, hipStream_t s) {
     hipLaunchKernelGGL(k_shift, ew_grid(count), dim3(kThreads), 0, s, count, src, shift, dst);
+    return hipGetLastError();
+}
+hipError_t launch_gauge(size_t count, const double* src, const double* sums, double inv, double* dst, hipStream_t s) {
+    const size_t pairs = count / 2, per = 4 * (size_t)kThreads;  // n^3 is even
+    const size_t blocks = (pairs + per - 1) / per;
+    hipLaunchKernelGGL(k_gauge, dim3((unsigned)(blocks < 1 ? 1 : blocks > 16384 ? 16384 : blocks)), dim3(kThreads), 0,
+                       s, pairs, reinterpret_cast<const double2*>(src), sums, inv, reinterpret_cast<double2*>(dst));
     return hipGetLastError();
 }
 template <typename T>
@@ -882,7 +918,7 @@ template hipError_t launch_convert<float, float>(size_t, const float*, float*, h
 
 #define INST_OUTER(TA, TR, TE, TC)                                                                                \
     template hipError_t launch_outer_residual<TA, TR, TE, TC>(const OpDesc<TC>&, const double*, const TE*, double*, \
-                                                              const double*, double, TR*, TR*, double, double*,     \
+                                                              const double*, Mean, TR*, TR*, double, double*,     \
                                                               hipStream_t, hipEvent_t, hipEvent_t);
 INST_OUTER(double, double, double, double)
 INST_OUTER(double, double, double, float)

@@ -86,13 +86,14 @@ struct mg_ctx {
     hipGraphExec_t coarse_exec = nullptr;
     int coarse_cur = 0;
     hipEvent_t norm_ev = nullptr;  // completion of the per-cycle norm readback
-    // The sums finished inside the pass from zero need no event: the block
+    // The outer sums need no event: the block
     // that writes them to the pinned mirror makes them visible at system
     // scope and then writes sums_seq to hscal[kHostFlagSlot], which the host
     // polls.  An event there cost a 5.6 us stall between the pass from zero
     // and the next kernel at 256^3 (4.6 us without its system-scope release).
     double sums_seq = 0.0;
     bool scal_flag = false;  // the pending readback is the flag, not norm_ev
+    double mean_seq = 0.0;   // number of the last readback of the sum of b
     bool use_pairs = true;         // last two steps of a smoothing pass in one two-step kernel
     bool use_visits = true;        // fused visits of the 32^3 and 64^3 levels (float hierarchy)
     bool use_tail = true;          // levels of at most 16^3 points in one workgroup
@@ -612,10 +613,21 @@ mg_status coarse_level(mg_ctx* c, int l) {
     return MG_OK;
 }
 
+// The pending outer sums as a job for the kernel about to be launched, which
+// then finishes them; count 0 when none are pending.
+SumsJob take_sums(mg_ctx* c) {
+    if (!c->pending_sums) return SumsJob{};
+    c->pending_sums = false;
+    c->scal_flag = true;
+    c->sums_seq += 1.0;
+    return SumsJob{c->partials, c->nparts_outer, 3, c->dscal, 1, c->hscal, c->sums_seq};
+}
+
 // The variable-coefficient levels from l0 down in one workgroup.
 template <typename T>
 mg_status var_tail_cycle(mg_ctx* c, int l0) {
     VarTailArgs<T> a{};
+    a.sums = take_sums(c);
     a.nlev = (int)c->lev.size() - l0;
     a.sched.cheb = c->p.smoother == MG_CHEBYSHEV ? 1 : 0;
     a.sched.steps = (int)c->lev[l0].a.size();
@@ -663,6 +675,7 @@ mg_status tail_cycle(mg_ctx* c, int l0) {
     }
     a.Q = c->Q;
     a.lam1 = c->lam1;
+    a.sums = take_sums(c);
     HIPCHK(c, launch_tail<T>(a, c->stream));
     // the tail writes the first tail level's result to that level's buffer x0
     c->lev[l0].cur = 0;
@@ -845,10 +858,11 @@ mg_status vcycle_from_zero(mg_ctx* c, int l) {
 
 // ---- outer residual dispatch ---------------------------------------------------------------
 // r = (b - mean b) - M phi (phi = phi_in + e when e != null); per-block r^2 sums into partials.
+// The sum of b is in device slot 0 (device_sum).
 // With next_cycle set, the kernel also writes the first smoothing step of the
 // V-cycle that follows (x = c0 D^-1 r on level 0).
 mg_status outer_residual(mg_ctx* c, const double* phi_in, const void* e, double* phi_out, const double* b,
-                         double bmean, bool next_cycle = false) {
+                         bool next_cycle = false) {
     Level& L = c->lev[0];
     const int n = L.n;
     const double ih2 = L.ih2;
@@ -861,6 +875,7 @@ mg_status outer_residual(mg_ctx* c, const double* phi_in, const void* e, double*
     mg_status st = time_events(c, true, MG_TIME_OUTER, &ev0, &ev1);
     if (st != MG_OK) return st;
     hipError_t err;
+    const Mean bmean{c->dscal, 1.0 / (double)L.N};  // the sum of b is in slot 0
     if (c->p.precision == MG_FP64) {
         OpDesc<double> op{n, ih2, (const double*)c->coeff_outer};
         err = launch_outer_residual<double, double, double, double>(op, phi_in, (const double*)e, phi_out, b, bmean,
@@ -1050,6 +1065,7 @@ static mg_status create_impl(mg_ctx* c, const void* coeff, int coeff_dtype, cons
     HIPCHK(c, hipHostMalloc((void**)&c->hscal, 16 * sizeof(double), hipHostMallocCoherent));
     HIPCHK(c, hipEventCreateWithFlags(&c->norm_ev, hipEventDisableTiming));
     c->hscal[kHostFlagSlot] = 0.0;
+    c->hscal[kHostMeanSlot] = 0.0;
 
     if (c->var) {
         // fine coefficients in double, validated, restricted level by level
@@ -1223,10 +1239,13 @@ mg_status mg_set_stream(mg_ctx* c, void* stream) {
     return MG_OK;
 }
 
-// mean of b into dscal[slot] (sum), then the caller divides
-static mg_status device_sum(mg_ctx* c, const double* u, double shift, int pw, int slot) {
+// sum of (u - shift)^pw into dscal[slot]; to_host: also into the host mirror,
+// for wait_mean
+static mg_status device_sum(mg_ctx* c, const double* u, double shift, int pw, int slot, bool to_host = false) {
     HIPCHK(c, launch_block_sums(c->p.n, u, shift, pw, c->partials, c->stream));
-    HIPCHK(c, launch_finalize_sum(c->partials, c->nparts, c->dscal, slot, c->stream));
+    if (to_host) c->mean_seq += 1.0;
+    HIPCHK(c, launch_finalize_sum(c->partials, c->nparts, c->dscal, slot, c->stream, to_host ? c->hscal : nullptr,
+                                  c->mean_seq));
     return MG_OK;
 }
 
@@ -1239,11 +1258,11 @@ static mg_status post_scalars(mg_ctx* c, int count) {
     return MG_OK;
 }
 // The three outer sums (slots 1..3), finalized straight into the pinned host
-// mirror as well; the event marks when the host may read them.
+// mirror as well; its flag slot marks when the host may read them.
 static mg_status post_outer_sums(mg_ctx* c) {
-    HIPCHK(c, launch_finalize_sums(c->partials, c->nparts_outer, 3, c->dscal, 1, c->stream, c->hscal));
-    HIPCHK(c, hipEventRecord(c->norm_ev, c->stream));
-    c->scal_flag = false;
+    c->sums_seq += 1.0;
+    c->scal_flag = true;
+    HIPCHK(c, launch_finalize_sums(c->partials, c->nparts_outer, 3, c->dscal, 1, c->stream, c->hscal, c->sums_seq));
     return MG_OK;
 }
 // Level 0's inner V-cycle starts with the pass-from-zero kernel, which can
@@ -1252,15 +1271,23 @@ static bool sums_in_pass_from_zero(const mg_ctx* c) {
     return c->fuse_sums && c->lev.size() > 1 && c->tail_start != 0 && !visit_level(c, 0, true) &&
            from_zero_triple(c, 0);
 }
+// The single-workgroup tail of the V-cycle that follows can finish them in a
+// second block (not inside a captured graph, whose arguments are fixed).  The
+// host gets them in the middle of the cycle, with the up-leg still to run
+// while it enqueues the next one; a launch of their own took 6 us a cycle and
+// its event another 5.
+static bool sums_in_tail(const mg_ctx* c) {
+    return c->fuse_sums && c->tail_start >= 0 && (!c->use_graph || c->tail_start == 0);
+}
 // Outer residual of the solve loop and its three sums.  When a V-cycle is
-// enqueued right after it (cycle_follows) and starts with the pass from zero,
-// the sums are left pending for that kernel; flush_sums finishes them
-// otherwise.  Either way norm_ev marks when the host may read them.
+// enqueued right after it (cycle_follows) and has a kernel that can finish
+// them (the pass from zero, or the tail), the sums are left pending for it;
+// flush_sums finishes them otherwise.
 static mg_status outer_with_sums(mg_ctx* c, const double* phi_in, const void* e, double* phi_out, const double* b,
-                                 double bmean, bool cycle_follows) {
-    mg_status st = outer_residual(c, phi_in, e, phi_out, b, bmean, true);
+                                 bool cycle_follows) {
+    mg_status st = outer_residual(c, phi_in, e, phi_out, b, true);
     if (st != MG_OK) return st;
-    if (cycle_follows && sums_in_pass_from_zero(c)) {
+    if (cycle_follows && (sums_in_pass_from_zero(c) || sums_in_tail(c))) {
         c->pending_sums = true;
         return MG_OK;
     }
@@ -1271,40 +1298,45 @@ static mg_status flush_sums(mg_ctx* c) {
     c->pending_sums = false;
     return post_outer_sums(c);
 }
-static mg_status wait_scalars(mg_ctx* c) {
-    if (!c->scal_flag) {
-        HIPCHK(c, hipEventSynchronize(c->norm_ev));
-        return MG_OK;
-    }
-    // Poll the flag.  Only after 50 ms of waiting is the stream asked whether
-    // it still runs: a stream query enqueues a marker, which costs a
-    // 5.8 us stall in front of the next kernel.
-    const volatile double* flag = c->hscal + kHostFlagSlot;
+// Waits until slot of the pinned mirror holds seq.  The slot is polled; only
+// after 50 ms of waiting is the stream asked whether it still runs: a stream
+// query enqueues a marker, which costs a 5.8 us stall in front of the next
+// kernel.
+static mg_status poll_host(mg_ctx* c, int slot, double seq) {
+    const volatile double* flag = c->hscal + slot;
     auto last = std::chrono::steady_clock::now();
     for (unsigned i = 1;; ++i) {
-        if (*flag == c->sums_seq) break;
+        if (*flag == seq) break;
         if ((i & 4095) != 0) continue;
         const auto now = std::chrono::steady_clock::now();
         if (now - last < std::chrono::milliseconds(50)) continue;
         last = now;
         const hipError_t e = hipStreamQuery(c->stream);
         if (e != hipSuccess && e != hipErrorNotReady) HIPCHK(c, e);
-        if (e == hipSuccess && *flag != c->sums_seq) return fail(c, MG_ERR_HIP, "outer sums flag not raised");
+        if (e == hipSuccess && *flag != seq) return fail(c, MG_ERR_HIP, "host flag not raised");
     }
     std::atomic_thread_fence(std::memory_order_acquire);
-    c->scal_flag = false;
     return MG_OK;
 }
+static mg_status wait_scalars(mg_ctx* c) {
+    if (!c->scal_flag) {
+        HIPCHK(c, hipEventSynchronize(c->norm_ev));
+        return MG_OK;
+    }
+    c->scal_flag = false;
+    return poll_host(c, kHostFlagSlot, c->sums_seq);
+}
+// the sum of b (device_sum with to_host) in hscal[0]
+static mg_status wait_mean(mg_ctx* c) { return poll_host(c, kHostMeanSlot, c->mean_seq); }
 
 static mg_status solve_impl(mg_ctx* c, double* phi, const double* b, double tol, int max_cycles,
                             mg_solve_info* info) {
     const size_t N0 = c->lev[0].N;
     const double invN = 1.0 / (double)N0;
     mg_status st;
-    if ((st = device_sum(c, b, 0.0, 1, 0)) != MG_OK) return st;
-    if ((st = read_scalars(c, 1)) != MG_OK) return st;
-    const double bmean = c->hscal[0] * invN;
-    if (!std::isfinite(bmean)) return fail(c, MG_ERR_NONFINITE, "source contains NaN or Inf");
+    // the outer kernels read the sum of b on the device; the host checks it
+    // with the first norms, before anything is written to phi
+    if ((st = device_sum(c, b, 0.0, 1, 0, true)) != MG_OK) return st;
     // the outer kernel also sums (b - bmean)^2 (slot 1) and phi (slot 3) beside r^2 (slot 2)
     // Look-ahead: the next V-cycle depends only on device data (the residual
     // just formed), so it is enqueued before the host waits for the norm; it
@@ -1312,9 +1344,15 @@ static mg_status solve_impl(mg_ctx* c, double* phi, const double* b, double tol,
     // look-ahead cycle that turns out unneeded only wrote hierarchy buffers.
     c->pending_sums = false;
     bool ahead = max_cycles > 0;
-    if ((st = outer_with_sums(c, phi, nullptr, nullptr, b, bmean, ahead)) != MG_OK) return st;
+    if ((st = outer_with_sums(c, phi, nullptr, nullptr, b, ahead)) != MG_OK) return st;
     if (ahead && (st = inner_vcycle(c)) != MG_OK) return st;
     if ((st = flush_sums(c)) != MG_OK) return st;
+    if ((st = wait_mean(c)) != MG_OK) return st;
+    if (!std::isfinite(c->hscal[0] * invN)) {
+        (void)hipStreamSynchronize(c->stream);
+        c->x1_ready = false;
+        return fail(c, MG_ERR_NONFINITE, "source contains NaN or Inf");
+    }
     if ((st = wait_scalars(c)) != MG_OK) return st;
     const double nb = std::sqrt(c->hscal[1]);
     if (info) {
@@ -1347,7 +1385,7 @@ static mg_status solve_impl(mg_ctx* c, double* phi, const double* b, double tol,
     while (rel > tol && cycles < max_cycles) {
         if (!ahead && (st = inner_vcycle(c)) != MG_OK) return st;
         ahead = cycles + 1 < max_cycles && rho * rel > tol;
-        if ((st = outer_with_sums(c, cur, inner_e(c), other, b, bmean, ahead)) != MG_OK) return st;
+        if ((st = outer_with_sums(c, cur, inner_e(c), other, b, ahead)) != MG_OK) return st;
         std::swap(cur, other);
         if (ahead && (st = inner_vcycle(c)) != MG_OK) return st;
         if ((st = flush_sums(c)) != MG_OK) return st;
@@ -1404,29 +1442,36 @@ mg_status mg_cycles(mg_ctx* c, double* phi, const double* b, int cycles, double*
     const size_t N0 = c->lev[0].N;
     const double invN = 1.0 / (double)N0;
     mg_status st;
-    if ((st = device_sum(c, b, 0.0, 1, 0)) != MG_OK) return st;
-    if ((st = read_scalars(c, 1)) != MG_OK) return st;
-    const double bmean = c->hscal[0] * invN;
-    if (!std::isfinite(bmean)) return fail(c, MG_ERR_NONFINITE, "source contains NaN or Inf");
+    if ((st = device_sum(c, b, 0.0, 1, 0, true)) != MG_OK) return st;
     c->pending_sums = false;
     double* cur = phi;
     double* other = c->phi_tmp;
     for (int k = 0; k <= cycles; ++k) {
+        // the last cycle's norms only are read: the others are not finished at all
         const bool follows = k < cycles;
-        if (k == 0) st = outer_with_sums(c, phi, nullptr, nullptr, b, bmean, follows);
-        else st = outer_with_sums(c, cur, inner_e(c), other, b, bmean, follows);
+        if (k == 0) st = outer_residual(c, phi, nullptr, nullptr, b, true);
+        else st = outer_residual(c, cur, inner_e(c), other, b, true);
         if (st != MG_OK) return st;
         if (k > 0) std::swap(cur, other);
         if (follows && (st = inner_vcycle(c)) != MG_OK) return st;
+        // the mean of b, before phi is overwritten; the first cycle is running
+        if (k == 0) {
+            if ((st = wait_mean(c)) != MG_OK) return st;
+            if (!std::isfinite(c->hscal[0] * invN)) {
+                (void)hipStreamSynchronize(c->stream);
+                c->x1_ready = false;
+                return fail(c, MG_ERR_NONFINITE, "source contains NaN or Inf");
+            }
+        }
     }
-    if ((st = flush_sums(c)) != MG_OK) return st;
-    if ((st = wait_scalars(c)) != MG_OK) return st;
+    if ((st = post_outer_sums(c)) != MG_OK) return st;
+    c->scal_flag = false;
+    // gauge from the sums on the device, so that one wait serves it and the norms
+    HIPCHK(c, launch_gauge(N0, cur, c->dscal, invN, phi, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     c->x1_ready = false;
     const double nb = std::sqrt(c->hscal[1]);
     const double rel = nb > 0.0 ? std::sqrt(c->hscal[2]) / nb : 0.0;
-    if (nb == 0.0) HIPCHK(c, launch_fill<double>(N0, 0.0, phi, c->stream));
-    else HIPCHK(c, launch_shift(N0, cur, c->hscal[3] * invN, phi, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
     if (rel_res_out) *rel_res_out = rel;
     if (!std::isfinite(rel)) return fail(c, MG_ERR_NONFINITE, "residual is not finite");
     return MG_OK;
@@ -1466,6 +1511,7 @@ mg_status pcg_impl(mg_ctx* c, double* phi, const double* b, double tol, int max_
     const int nb = pcg_blocks(n);
     mg_status st;
     c->x1_ready = false;
+    c->pending_sums = false;
     if ((st = device_sum(c, b, 0.0, 1, 0)) != MG_OK) return st;
     if ((st = read_scalars(c, 1)) != MG_OK) return st;
     const double bmean = c->hscal[0] * invN;
@@ -1652,16 +1698,15 @@ mg_status mg_vcycle(mg_ctx* c, double* phi, const double* b, double* rel_res_out
     const size_t N0 = c->lev[0].N;
     const double invN = 1.0 / (double)N0;
     mg_status st;
+    c->pending_sums = false;
     if ((st = device_sum(c, b, 0.0, 1, 0)) != MG_OK) return st;
-    if ((st = read_scalars(c, 1)) != MG_OK) return st;
-    const double bmean = c->hscal[0] * invN;
-    if ((st = outer_residual(c, phi, nullptr, nullptr, b, bmean, true)) != MG_OK) return st;
+    if ((st = outer_residual(c, phi, nullptr, nullptr, b, true)) != MG_OK) return st;
     if ((st = inner_vcycle(c)) != MG_OK) return st;
     const void* e = inner_e(c);
     if (c->inner_double) HIPCHK(c, launch_add<double>(N0, phi, (const double*)e, phi, c->stream));
     else HIPCHK(c, launch_add<float>(N0, phi, (const float*)e, phi, c->stream));
     if (rel_res_out) {
-        if ((st = outer_residual(c, phi, nullptr, nullptr, b, bmean)) != MG_OK) return st;
+        if ((st = outer_residual(c, phi, nullptr, nullptr, b)) != MG_OK) return st;
         HIPCHK(c, launch_finalize_sums(c->partials, c->nparts_outer, 3, c->dscal, 1, c->stream));
         if ((st = read_scalars(c, 3)) != MG_OK) return st;
         const double nb = std::sqrt(c->hscal[1]);

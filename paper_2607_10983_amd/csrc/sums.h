@@ -27,6 +27,17 @@ struct SumsJob {
 // Slot of the pinned host mirror that receives SumsJob::seq.
 constexpr int kHostFlagSlot = 15;
 
+// Slot that receives the number of the mean's readback (launch_finalize_sum).
+constexpr int kHostMeanSlot = 14;
+
+// Mean of a field from its device sum: the outer kernels read it themselves, so
+// a solve starts without a host round trip for it.
+struct Mean {
+    const double* sum;
+    double inv;  // 1 / number of points
+    __device__ __forceinline__ double get() const { return *sum * inv; }
+};
+
 // Every thread of the block calls it; sh holds kSumLanes doubles.
 __device__ __forceinline__ void finish_sums(const SumsJob& job, double* sh) {
     const int nt = blockDim.x * blockDim.y * blockDim.z;

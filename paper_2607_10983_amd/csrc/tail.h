@@ -4,6 +4,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "sums.h"
+
 namespace mg {
 
 constexpr int kTailMaxLevels = 4;
@@ -30,6 +32,7 @@ struct TailArgs {
     TailSchedule sched;
     const double* Q;               // coarsest separable basis (nc x nc)
     const double* lam1;            // its 1-D eigenvalues
+    SumsJob sums;                  // count > 0: outer sums finished by a second block
 };
 
 template <typename T>

@@ -321,6 +321,10 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<T> A) {
     __shared__ double sB[512];
     __shared__ double q[64];
     __shared__ double lam[8];
+    if (blockIdx.x == 1) {  // the outer sums, beside the tail
+        finish_sums(A.sums, reinterpret_cast<double*>(fields));
+        return;
+    }
     const Fields<T> F{fields, &A};
     unsigned curbits = 0;  // bit l: buffer holding level l's iterate (no private array)
     const int nl = A.nlev;
@@ -376,7 +380,8 @@ hipError_t launch_tail(const TailArgs<T>& args, hipStream_t s) {
     int elems = 0;
     for (int l = 0; l < args.nlev; ++l) elems += 3 * args.n[l] * args.n[l] * args.n[l];
     if (elems > kTailElems) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_tail<T>), dim3(1), dim3(kTailThreads), 0, s, args);
+    static_assert(sizeof(T) * kTailElems >= kSumLanes * sizeof(double), "the sums fit the tail's LDS");
+    hipLaunchKernelGGL((k_tail<T>), dim3(args.sums.count > 0 ? 2 : 1), dim3(kTailThreads), 0, s, args);
     return hipGetLastError();
 }
 

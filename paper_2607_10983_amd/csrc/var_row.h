@@ -5,6 +5,8 @@
 
 #include <cstddef>
 
+#include "sums.h"
+
 namespace mg {
 
 bool var_row_kernels_apply(int n);
@@ -31,7 +33,7 @@ hipError_t launch_var_resid_row(int n, double ih2, const TC* C, const T* x, cons
                                 hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 template <typename TA, typename TR, typename TE, typename TC>
 hipError_t launch_var_outer_row(int n, double ih2, const TC* C, const double* phi_in, const TE* e, double* phi_out,
-                                const double* b, double bmean, TR* r, TR* x1, double c0, double* partials,
+                                const double* b, Mean bmean, TR* r, TR* x1, double c0, double* partials,
                                 hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
 }  // namespace mg

@@ -676,9 +676,10 @@ template <typename TA, typename TR, typename TE, typename TC, int VEC, bool UPDA
 __global__ __launch_bounds__(kBlock) void k_var_outer_row(int n, TA ih2, const TC* __restrict__ C,
                                                           const double* __restrict__ phi_in,
                                                           const TE* __restrict__ e, double* __restrict__ phi_out,
-                                                          const double* __restrict__ b, double bmean,
+                                                          const double* __restrict__ b, Mean bm,
                                                           TR* __restrict__ r, TR* __restrict__ x1, TA c0,
                                                           double* __restrict__ partials, int nz, int nyb) {
+    const double bmean = bm.get();
     __shared__ double sh[3 * kWaves];
     const RowGrid g{64 * VEC, 64 * VEC - 1};
     constexpr size_t N = (size_t)(64 * VEC) * (64 * VEC) * (64 * VEC);
@@ -914,7 +915,7 @@ hipError_t launch_var_resid_row(int n, double ih2, const TC* C, const T* x, cons
 
 template <typename TA, typename TR, typename TE, typename TC>
 hipError_t launch_var_outer_row(int n, double ih2, const TC* C, const double* phi_in, const TE* e, double* phi_out,
-                                const double* b, double bmean, TR* r, TR* x1, double c0, double* partials,
+                                const double* b, Mean bmean, TR* r, TR* x1, double c0, double* partials,
                                 hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     int nz, nyb, blocks;
     shape(n, nz, nyb, blocks);
@@ -944,7 +945,7 @@ INST_VAR(float, double)
 
 #define INST_VOUT(TA, TR, TE, TC)                                                                                  \
     template hipError_t launch_var_outer_row<TA, TR, TE, TC>(int, double, const TC*, const double*, const TE*,     \
-                                                             double*, const double*, double, TR*, TR*, double,     \
+                                                             double*, const double*, Mean, TR*, TR*, double,     \
                                                              double*, hipStream_t, hipEvent_t, hipEvent_t);
 INST_VOUT(double, double, double, double)
 INST_VOUT(double, double, double, float)

@@ -18,6 +18,7 @@ struct VarTailArgs {
     T* x;                        // its V-cycle result
     const double* G;             // dense pseudo-inverse of the coarsest operator
     TailSchedule sched;
+    SumsJob sums;                // count > 0: outer sums finished by a second block
 };
 
 // Levels of 16^3 and 8^3 points (or one of them) above a coarsest level of

@@ -406,6 +406,11 @@ __global__ __launch_bounds__(tail_threads<T>()) void k_var_tail(VarTailArgs<T> A
     constexpr bool REG = Lds<T>::kReg;
     constexpr int NT = tail_threads<T>(), NS = kSegs / NT;  // segments of 16^3 per thread
     __shared__ __align__(16) Lds<T> S;
+    if (blockIdx.x == 1) {  // the outer sums, beside the tail
+        static_assert(sizeof(S.x16) >= kSumLanes * sizeof(double), "the sums fit the tail's LDS");
+        finish_sums(A.sums, reinterpret_cast<double*>(S.x16));
+        return;
+    }
     const int t = threadIdx.x;
     const int steps = A.sched.steps;
     const bool cheb = A.sched.cheb != 0;
@@ -622,9 +627,10 @@ hipError_t launch_var_tail(const VarTailArgs<T>& a, hipStream_t s) {
     if (a.nlev < 2 || a.nlev > 3 || a.sched.steps < 1 || a.sched.steps > kTailMaxSteps ||
         !var_tail_applies(a.n[0], a.n[a.nlev - 1], a.nlev))
         return hipErrorInvalidValue;
-    if (a.n[0] == 8) hipLaunchKernelGGL((k_var_tail<T, false, false>), dim3(1), dim3(tail_threads<T>()), 0, s, a);
-    else if (a.n[a.nlev - 1] == 4) hipLaunchKernelGGL((k_var_tail<T, true, false>), dim3(1), dim3(tail_threads<T>()), 0, s, a);
-    else hipLaunchKernelGGL((k_var_tail<T, true, true>), dim3(1), dim3(tail_threads<T>()), 0, s, a);
+    const dim3 grid(a.sums.count > 0 ? 2 : 1);
+    if (a.n[0] == 8) hipLaunchKernelGGL((k_var_tail<T, false, false>), grid, dim3(tail_threads<T>()), 0, s, a);
+    else if (a.n[a.nlev - 1] == 4) hipLaunchKernelGGL((k_var_tail<T, true, false>), grid, dim3(tail_threads<T>()), 0, s, a);
+    else hipLaunchKernelGGL((k_var_tail<T, true, true>), grid, dim3(tail_threads<T>()), 0, s, a);
     return hipGetLastError();
 }
 
