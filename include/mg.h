@@ -43,6 +43,8 @@
 #ifndef MG_H
 #define MG_H
 
+#include <stddef.h>
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -147,6 +149,33 @@ mg_status mg_create(const mg_params* p, const void* coeff, int coeff_dtype,
  * potential folds a coarse level's mesh (a diagonal coefficient <= 0 or not
  * finite there). */
 mg_status mg_create_psi(const mg_params* p, const double* psi, void* stream, mg_ctx** out);
+
+/* What a context is built from: nothing (seven-point), a coefficient field in
+ * float or double (mg_create), or a deformation potential (mg_create_psi). */
+enum mg_source {
+    MG_SOURCE_FLAT = 0,
+    MG_SOURCE_COEFF_F32 = 1,
+    MG_SOURCE_COEFF_F64 = 2,
+    MG_SOURCE_PSI = 3
+};
+
+/* Device memory a context of these parameters and source (enum mg_source)
+ * lives in (*keep_bytes) and needs besides during its creation
+ * (*setup_bytes).  Host only.  Errors: MG_ERR_INVALID. */
+mg_status mg_workspace_bytes(const mg_params* p, int source, size_t* keep_bytes, size_t* setup_bytes);
+
+/* mg_create / mg_create_psi in caller-owned device memory, for programs that
+ * have an allocator of their own (a moving mesh creates a context every step,
+ * and a device allocation of this size takes milliseconds).  field: the
+ * coefficients or the potential (NULL for MG_SOURCE_FLAT), read during the
+ * call only.  keep (at least keep_bytes of mg_workspace_bytes, 16-byte
+ * aligned) belongs to the context until mg_destroy returns; setup (at least
+ * setup_bytes) is free again on return, which is after the stream has
+ * finished with it.  mg_solve_pcg and the single-step entry points still
+ * allocate their own work fields on first use.  Errors as mg_create, and
+ * MG_ERR_INVALID for memory that is too small or missing. */
+mg_status mg_create_in(const mg_params* p, int source, const void* field, void* keep, size_t keep_bytes,
+                       void* setup, size_t setup_bytes, void* stream, mg_ctx** out);
 
 /* Free everything the context owns.  NULL is accepted. */
 mg_status mg_destroy(mg_ctx* ctx);

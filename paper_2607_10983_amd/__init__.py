@@ -112,23 +112,34 @@ class Multigrid:
         self.var = coeff is not None or psi is not None
         if coeff is not None and psi is not None:
             raise ValueError("give coeff or psi, not both")
-        cptr, cdt = None, _lib.MG_DTYPE_F64
+        source, src, where = _lib.MG_SOURCE_FLAT, None, "mg_create"
         if coeff is not None:
             if coeff.dtype not in (torch.float32, torch.float64):
                 raise ValueError("coeff must be float32 or float64")
             _check_field(coeff, self.n, coeff.dtype, "coeff", comps=6)
-            cptr = _ptr(coeff)
-            cdt = _lib.MG_DTYPE_F64 if coeff.dtype == torch.float64 else _lib.MG_DTYPE_F32
-        h_ctx = ctypes.c_void_p()
+            src = _ptr(coeff)
+            source = _lib.MG_SOURCE_COEFF_F64 if coeff.dtype == torch.float64 else _lib.MG_SOURCE_COEFF_F32
         if psi is not None:
             _check_field(psi, self.n, torch.float64, "psi")
-            st = lib.mg_create_psi(ctypes.byref(p), _ptr(psi), _stream_ptr(), ctypes.byref(h_ctx))
-            if st != _lib.MG_OK:
-                raise MGError(st, "mg_create_psi")
-        else:
-            st = lib.mg_create(ctypes.byref(p), cptr, cdt, _stream_ptr(), ctypes.byref(h_ctx))
-            if st != _lib.MG_OK:
-                raise MGError(st, "mg_create")
+            source, src, where = _lib.MG_SOURCE_PSI, _ptr(psi), "mg_create_psi"
+        # the context lives in memory of torch's caching allocator: a program
+        # that creates one per time step gets the same block back at once
+        keep_n, setup_n = ctypes.c_size_t(0), ctypes.c_size_t(0)
+        st = lib.mg_workspace_bytes(ctypes.byref(p), source, ctypes.byref(keep_n), ctypes.byref(setup_n))
+        if st != _lib.MG_OK:
+            raise MGError(st, where)
+        try:
+            keep = torch.empty(keep_n.value, dtype=torch.uint8, device="cuda")
+            setup = torch.empty(setup_n.value, dtype=torch.uint8, device="cuda")
+        except torch.cuda.OutOfMemoryError as e:
+            raise MGError(_lib.MG_ERR_NOMEM, where, str(e)) from None
+        self._stream = torch.cuda.current_stream()
+        h_ctx = ctypes.c_void_p()
+        st = lib.mg_create_in(ctypes.byref(p), source, src, _ptr(keep), keep_n, _ptr(setup) if setup_n.value else None,
+                              setup_n, _stream_ptr(), ctypes.byref(h_ctx))
+        if st != _lib.MG_OK:
+            raise MGError(st, where)
+        self._keep = keep
         self._ctx = h_ctx
 
     # ---------------------------------------------------------------- lifecycle
@@ -136,6 +147,7 @@ class Multigrid:
         if getattr(self, "_ctx", None):
             _lib.load().mg_destroy(self._ctx)
             self._ctx = None
+            self._keep = None
 
     def __del__(self):
         try:
@@ -148,7 +160,10 @@ class Multigrid:
         return MGError(st, where, detail)
 
     def _sync_stream(self):
-        _lib.load().mg_set_stream(self._ctx, _stream_ptr())
+        stream = _torch().cuda.current_stream()
+        if stream != self._stream:  # the allocator must not hand the block out while this stream uses it
+            self._keep.record_stream(stream)
+        _lib.load().mg_set_stream(self._ctx, ctypes.c_void_p(stream.cuda_stream))
 
     # ---------------------------------------------------------------- solves
     def solve(self, b, phi0=None, tol: float = 1e-10, max_cycles: int = 50, history: bool = True,

@@ -18,6 +18,7 @@ MG_ERR_NOT_CONVERGED = 6
 MG_FP64, MG_MIXED, MG_FP32 = 0, 1, 2
 MG_CHEBYSHEV, MG_JACOBI = 0, 1
 MG_DTYPE_F32, MG_DTYPE_F64 = 0, 1
+MG_SOURCE_FLAT, MG_SOURCE_COEFF_F32, MG_SOURCE_COEFF_F64, MG_SOURCE_PSI = 0, 1, 2, 3
 MG_NOALLOC_MAX_N = 512
 MG_PREDICT_RECYCLE, MG_PREDICT_GROWTH, MG_PREDICT_LINEAR, MG_PREDICT_QUADRATIC = 0, 1, 2, 3
 MG_TIME_STEP, MG_TIME_PAIR, MG_TIME_TRIPLE, MG_TIME_OUTER, MG_TIME_TRANSFER = 1, 2, 4, 8, 16
@@ -63,6 +64,10 @@ SIGNATURES = {
     "mg_validate_params": (_I, [ctypes.POINTER(MgParams)]),
     "mg_create": (_I, [ctypes.POINTER(MgParams), _P, _I, _P, ctypes.POINTER(_P)]),
     "mg_create_psi": (_I, [ctypes.POINTER(MgParams), _P, _P, ctypes.POINTER(_P)]),
+    "mg_workspace_bytes": (_I, [ctypes.POINTER(MgParams), _I, ctypes.POINTER(ctypes.c_size_t),
+                                ctypes.POINTER(ctypes.c_size_t)]),
+    "mg_create_in": (_I, [ctypes.POINTER(MgParams), _I, _P, _P, ctypes.c_size_t, _P, ctypes.c_size_t, _P,
+                          ctypes.POINTER(_P)]),
     "mg_destroy": (_I, [_P]),
     "mg_set_stream": (_I, [_P, _P]),
     "mg_vcycle": (_I, [_P, _P, _P, _PD]),

@@ -53,10 +53,6 @@ hipError_t launch_residual_restrict(const OpDesc<TC>& op, const T* x, const T* b
                                     T* scratch, hipStream_t s, hipEvent_t ev0 = nullptr,
                                     hipEvent_t ev1 = nullptr, const FirstStep<T>& first = FirstStep<T>());
 
-// coarse = R(fine), componentwise for `ncomp` consecutive fields.
-template <typename T>
-hipError_t launch_restrict(int n, const T* fine, T* coarse, int ncomp, hipStream_t s);
-
 // ---- prolongation ------------------------------------------------------------
 // x (n^3) += P e ((n/2)^3), trilinear.
 template <typename T>
@@ -95,10 +91,6 @@ hipError_t launch_finalize_sums(const double* partials, int count, int arrays, d
 // host_out also host_out[slot], then seq into host_out[kHostMeanSlot].
 hipError_t launch_finalize_sum(const double* partials, int count, double* out, int slot,
                                hipStream_t s, double* host_out = nullptr, double seq = 0.0);
-// out[slot] = max_{i < count} partials[i].
-hipError_t launch_finalize_max(const double* partials, int count, double* out, int slot,
-                               hipStream_t s);
-
 // ---- elementwise -----------------------------------------------------------------
 // dst = src - shift (double, may alias)
 hipError_t launch_shift(size_t count, const double* src, double shift, double* dst, hipStream_t s);
@@ -112,14 +104,6 @@ template <typename TD, typename TS>
 hipError_t launch_convert(size_t count, const TS* src, TD* dst, hipStream_t s);
 template <typename T>
 hipError_t launch_fill(size_t count, T value, T* dst, hipStream_t s);
-
-// ---- coefficient hierarchy -------------------------------------------------------
-// partials[block] = max over the block of the Gershgorin bound of D^-1 M.
-template <typename TC>
-hipError_t launch_gershgorin(const OpDesc<TC>& op, double* partials, hipStream_t s);
-// partials[block] = number of cells with a non-finite component or C^{aa} <= 0.
-template <typename TC>
-hipError_t launch_coeff_check(int n, const TC* coeff, double* partials, hipStream_t s);
 
 // ---- coarsest level ----------------------------------------------------------------
 // Seven-point operator: e = Q diag(1/lambda) Q^T r with the separable real
@@ -138,9 +122,6 @@ hipError_t launch_coarse_dense(int N, const double* G, const T* r, T* e, hipStre
 template <typename TO>
 hipError_t launch_coeff_grad(int n, double ih2, const double* lam, const double* phi, TO* cbar,
                              hipStream_t s);
-template <typename TO>
-hipError_t launch_geometry(int n, double ih2, const double* psi, TO* C, double* sqrtg,
-                           hipStream_t s);
 // Jbar (symmetric storage: off-diagonal = Jbar_ab + Jbar_ba) of the planes
 // zlo .. zlo + planes - 1 (mod n), 6 planes n^2 doubles laid out [c][plane][y][x];
 // planes = 0: the whole grid (6 n^3 doubles, zlo = 0).

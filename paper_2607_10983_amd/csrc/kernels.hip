@@ -110,8 +110,7 @@ __global__ __launch_bounds__(kThreads) void k_resid_restrict(int n, T ih2, const
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_restrict(int n, const T* __restrict__ fine,
                                                        T* __restrict__ coarse, int nz,
-                                                       const T* __restrict__ cC = nullptr, T* cx1 = nullptr,
-                                                       T cc0 = T(0), T cih2 = T(0)) {
+                                                       const T* __restrict__ cC, T* cx1, T cc0, T cih2) {
     const int nc = n >> 1;
     const Grid g{n, n - 1};
     const Grid gc{nc, nc - 1};
@@ -261,12 +260,12 @@ __global__ __launch_bounds__(kThreads) void k_block_sums(int n, const double* __
 }
 
 __global__ __launch_bounds__(1024) void k_finalize(const double* __restrict__ partials, int count, double* out,
-                                                   int slot, int is_max, double* host_out, double seq) {
+                                                   int slot, double* host_out, double seq) {
     __shared__ double sh[1024];
     const int tid = threadIdx.x;
-    double v = is_max ? -INFINITY : 0.0;
-    for (int i = tid; i < count; i += 1024) v = is_max ? fmax(v, partials[i]) : v + partials[i];
-    const double r = is_max ? block_max(v, sh) : block_sum(v, sh);
+    double v = 0.0;
+    for (int i = tid; i < count; i += 1024) v += partials[i];
+    const double r = block_sum(v, sh);
     if (tid == 0) {
         out[slot] = r;
         if (host_out) {  // pinned host mirror, then the flag the host polls
@@ -331,68 +330,6 @@ dim3 ew_grid(size_t count) {
     if (b > 65536) b = 65536;
     if (b == 0) b = 1;
     return dim3((unsigned)b);
-}
-
-// =====================================================================================
-// coefficient checks and Gershgorin bounds
-// =====================================================================================
-template <typename TC>
-__global__ __launch_bounds__(kThreads) void k_gershgorin(int n, const TC* __restrict__ C, double* partials, int nz) {
-    __shared__ double sh[kThreads];
-    const Grid g{n, n - 1};
-    const size_t N = (size_t)n * n * n;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z0 = blockIdx.z * nz;
-    double m = -INFINITY;
-    for (int z = z0; z < z0 + nz; ++z) {
-        const size_t i0 = g(x, y, z);
-        double face = 0.0;
-        for (int a = 0; a < 3; ++a) {
-            const TC* c = C + a * N;
-            const int dx = a == 0, dy = a == 1, dz = a == 2;
-            const double c0 = (double)c[i0];
-            face += 0.5 * (c0 + (double)c[g(x + dx, y + dy, z + dz)]) + 0.5 * (c0 + (double)c[g(x - dx, y - dy, z - dz)]);
-        }
-        double edge = 0.0;
-        const int pa[3] = {0, 0, 1}, pb[3] = {1, 2, 2};
-        for (int p = 0; p < 3; ++p) {
-            const TC* c = C + (3 + p) * N;
-            for (int sa = -1; sa <= 1; sa += 2)
-                for (int sb = -1; sb <= 1; sb += 2) {
-                    int ax = 0, ay = 0, az = 0, bx = 0, by = 0, bz = 0;
-                    (pa[p] == 0 ? ax : pa[p] == 1 ? ay : az) = sa;
-                    (pb[p] == 0 ? bx : pb[p] == 1 ? by : bz) = sb;
-                    edge += fabs((double)c[g(x + ax, y + ay, z + az)] + (double)c[g(x + bx, y + by, z + bz)]) * 0.25;
-                }
-        }
-        m = fmax(m, 1.0 + (face + edge) / face);
-    }
-    const double tot = block_max(m, sh);
-    if (lin_tid() == 0) partials[lin_bid()] = tot;
-}
-
-template <typename TC>
-__global__ __launch_bounds__(kThreads) void k_coeff_check(int n, const TC* __restrict__ C, double* partials, int nz) {
-    __shared__ double sh[kThreads];
-    const Grid g{n, n - 1};
-    const size_t N = (size_t)n * n * n;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z0 = blockIdx.z * nz;
-    double bad = 0.0;
-    for (int z = z0; z < z0 + nz; ++z) {
-        const size_t i = g(x, y, z);
-        bool ok = true;
-        for (int c = 0; c < 6; ++c) {
-            const double v = (double)C[c * N + i];
-            if (!isfinite(v)) ok = false;
-            if (c < 3 && !(v > 0.0)) ok = false;
-        }
-        bad += ok ? 0.0 : 1.0;
-    }
-    const double tot = block_sum(bad, sh);
-    if (lin_tid() == 0) partials[lin_bid()] = tot;
 }
 
 // =====================================================================================
@@ -546,33 +483,6 @@ __global__ __launch_bounds__(kThreads) void k_coeff_grad(int n, double ih2, cons
 // =====================================================================================
 // moving-mesh geometry
 // =====================================================================================
-template <typename TO>
-__global__ __launch_bounds__(kThreads) void k_geometry(int n, double ih2, const double* __restrict__ psi,
-                                                       TO* __restrict__ C, double* __restrict__ sqrtg, int nz) {
-    const Grid g{n, n - 1};
-    const size_t N = (size_t)n * n * n;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z0 = blockIdx.z * nz;
-    for (int z = z0; z < z0 + nz; ++z) {
-        double H[6];
-        hess_at(psi, g, x, y, z, ih2, H);
-        H[0] += 1.0; H[1] += 1.0; H[2] += 1.0;
-        Sym3 J, K, K2;
-        sym_from6(H, J);
-        const double det = inv3(J, K);
-        mul3(K, K, K2);   // J symmetric: J^-1 J^-T = K K
-        const size_t i = g(x, y, z);
-        C[i] = (TO)(det * K2.m[0][0]);
-        C[N + i] = (TO)(det * K2.m[1][1]);
-        C[2 * N + i] = (TO)(det * K2.m[2][2]);
-        C[3 * N + i] = (TO)(det * K2.m[0][1]);
-        C[4 * N + i] = (TO)(det * K2.m[0][2]);
-        C[5 * N + i] = (TO)(det * K2.m[1][2]);
-        if (sqrtg) sqrtg[i] = det;
-    }
-}
-
 // Per cell: Jbar = t K - d (P + P^T), P = K G K^2, t = d <G, K^2> + sqrtgbar d,
 // G the full symmetric cotangent of C (stored off-diagonals halved).
 // Jbar of the planes zlo .. zlo + planes - 1 (mod n): plane p of component c
@@ -726,16 +636,6 @@ hipError_t launch_residual_restrict(const OpDesc<TC>& op, const T* x, const T* b
 }
 
 template <typename T>
-hipError_t launch_restrict(int n, const T* fine, T* coarse, int ncomp, hipStream_t s) {
-    Shape sh = stencil_shape(n / 2);
-    const size_t Nf = (size_t)n * n * n, Nc = Nf / 8;
-    for (int c = 0; c < ncomp; ++c)
-        hipLaunchKernelGGL((k_restrict<T>), sh.grid, sh.block, 0, s, n, fine + c * Nf, coarse + c * Nc, sh.nz,
-                           (const T*)nullptr, (T*)nullptr, T(0), T(0));
-    return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_prolong_add(int n, const T* e, T* x, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     if (row_kernels_apply(n)) return launch_prolong_row<T>(n, e, x, s, ev0, ev1);
     Shape sh = stencil_shape(n);
@@ -781,7 +681,7 @@ hipError_t launch_block_sums(int n, const double* u, double shift, int p, double
 }
 hipError_t launch_finalize_sum(const double* partials, int count, double* out, int slot, hipStream_t s,
                                double* host_out, double seq) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, partials, count, out, slot, 0, host_out, seq);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, partials, count, out, slot, host_out, seq);
     return hipGetLastError();
 }
 hipError_t launch_finalize_sums(const double* partials, int count, int arrays, double* out, int slot,
@@ -790,11 +690,6 @@ hipError_t launch_finalize_sums(const double* partials, int count, int arrays, d
     hipLaunchKernelGGL(k_finalize_multi, dim3(1), dim3(kSumLanes), 0, s, job);
     return hipGetLastError();
 }
-hipError_t launch_finalize_max(const double* partials, int count, double* out, int slot, hipStream_t s) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, partials, count, out, slot, 1, (double*)nullptr, 0.0);
-    return hipGetLastError();
-}
-
 hipError_t launch_shift(size_t count, const double* src, double shift, double* dst, hipStream_t s) {
     hipLaunchKernelGGL(k_shift, ew_grid(count), dim3(kThreads), 0, s, count, src, shift, dst);
     return hipGetLastError();
@@ -822,19 +717,6 @@ hipError_t launch_fill(size_t count, T value, T* dst, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <typename TC>
-hipError_t launch_gershgorin(const OpDesc<TC>& op, double* partials, hipStream_t s) {
-    Shape sh = stencil_shape(op.n);
-    hipLaunchKernelGGL((k_gershgorin<TC>), sh.grid, sh.block, 0, s, op.n, op.coeff, partials, sh.nz);
-    return hipGetLastError();
-}
-template <typename TC>
-hipError_t launch_coeff_check(int n, const TC* coeff, double* partials, hipStream_t s) {
-    Shape sh = stencil_shape(n);
-    hipLaunchKernelGGL((k_coeff_check<TC>), sh.grid, sh.block, 0, s, n, coeff, partials, sh.nz);
-    return hipGetLastError();
-}
-
 template <typename T>
 hipError_t launch_coarse_flat(int nc, const double* Q, const double* lam1, const T* r, T* e, hipStream_t s) {
     switch (nc) {
@@ -857,12 +739,6 @@ template <typename TO>
 hipError_t launch_coeff_grad(int n, double ih2, const double* lam, const double* phi, TO* cbar, hipStream_t s) {
     Shape sh = stencil_shape(n);
     hipLaunchKernelGGL((k_coeff_grad<TO>), sh.grid, sh.block, 0, s, n, ih2, lam, phi, cbar, sh.nz);
-    return hipGetLastError();
-}
-template <typename TO>
-hipError_t launch_geometry(int n, double ih2, const double* psi, TO* C, double* sqrtg, hipStream_t s) {
-    Shape sh = stencil_shape(n);
-    hipLaunchKernelGGL((k_geometry<TO>), sh.grid, sh.block, 0, s, n, ih2, psi, C, sqrtg, sh.nz);
     return hipGetLastError();
 }
 hipError_t launch_geometry_bwd_cell(int n, double ih2, const double* psi, const double* Cbar, const double* sbar,
@@ -898,16 +774,12 @@ INST_T_TC(double, float)
 INST_T_TC(float, double)
 
 #define INST_T(T)                                                                                  \
-    template hipError_t launch_restrict<T>(int, const T*, T*, int, hipStream_t);                   \
     template hipError_t launch_prolong_add<T>(int, const T*, T*, hipStream_t, hipEvent_t, hipEvent_t); \
     template hipError_t launch_add<T>(size_t, const double*, const T*, double*, hipStream_t);      \
     template hipError_t launch_fill<T>(size_t, T, T*, hipStream_t);                                \
-    template hipError_t launch_gershgorin<T>(const OpDesc<T>&, double*, hipStream_t);              \
-    template hipError_t launch_coeff_check<T>(int, const T*, double*, hipStream_t);                \
     template hipError_t launch_coarse_flat<T>(int, const double*, const double*, const T*, T*, hipStream_t); \
     template hipError_t launch_coarse_dense<T>(int, const double*, const T*, T*, hipStream_t);     \
-    template hipError_t launch_coeff_grad<T>(int, double, const double*, const double*, T*, hipStream_t); \
-    template hipError_t launch_geometry<T>(int, double, const double*, T*, double*, hipStream_t);
+    template hipError_t launch_coeff_grad<T>(int, double, const double*, const double*, T*, hipStream_t);
 INST_T(float)
 INST_T(double)
 

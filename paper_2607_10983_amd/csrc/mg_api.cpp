@@ -13,11 +13,14 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
 #include "flat_row.h"
 #include "kernels.h"
+#include "setup.h"
 #include "tail.h"
 #include "var_row.h"
 #include "var_tail.h"
@@ -48,6 +51,10 @@ struct TimingPair {
     hipEvent_t start, stop;
 };
 
+// Integer results of the setup kernels: bounds per level (bits of a double),
+// invalid cells per level from 16, invalid entries of the coarsest inverse at 32.
+constexpr int kSetupSlots = 33;
+
 }  // namespace
 
 struct mg_ctx {
@@ -59,7 +66,8 @@ struct mg_ctx {
     // fine-level coefficients used by the outer residual
     void* coeff_outer = nullptr;
     bool coeff_outer_double = true;
-    bool coeff_outer_owned = false;
+    void* mem = nullptr;        // the context's device memory when it owns it
+    u64* slots = nullptr;       // integer results of the setup kernels
     double* phi_tmp = nullptr;  // second buffer for the phi update
     double* partials = nullptr;
     int nparts = 0;        // partial sums written by launch_block_sums on the fine grid
@@ -85,7 +93,7 @@ struct mg_ctx {
     hipGraph_t coarse_graph = nullptr;
     hipGraphExec_t coarse_exec = nullptr;
     int coarse_cur = 0;
-    hipEvent_t norm_ev = nullptr;  // completion of the per-cycle norm readback
+    hipEvent_t norm_ev = nullptr;  // completion of a scalar readback (conjugate gradients)
     // The outer sums need no event: the block
     // that writes them to the pinned mirror makes them visible at system
     // scope and then writes sums_seq to hscal[kHostFlagSlot], which the host
@@ -200,86 +208,46 @@ void flat_basis(int nc, double hc, std::vector<double>& Q, std::vector<double>& 
     lam[nc - 1] = eig(nc / 2);
 }
 
-// Dense matrix of the 19-point operator on the coarsest level (host, double).
-void assemble_dense(int n, double ih2, const std::vector<double>& C, std::vector<double>& M) {
-    const int N = n * n * n;
-    M.assign((size_t)N * N, 0.0);
-    auto id = [n](int x, int y, int z) { return (((z % n + n) % n) * n + ((y % n + n) % n)) * n + ((x % n + n) % n); };
-    auto cc = [&](int c, int x, int y, int z) { return C[(size_t)c * N + id(x, y, z)]; };
-    for (int z = 0; z < n; ++z)
-        for (int y = 0; y < n; ++y)
-            for (int x = 0; x < n; ++x) {
-                const int i = id(x, y, z);
-                const int p[3] = {x, y, z};
-                for (int a = 0; a < 3; ++a)
-                    for (int s = -1; s <= 1; s += 2) {
-                        int q[3] = {p[0], p[1], p[2]};
-                        q[a] += s;
-                        const double cf = 0.5 * (cc(a, x, y, z) + cc(a, q[0], q[1], q[2]));
-                        M[(size_t)i * N + id(q[0], q[1], q[2])] += cf * ih2;
-                        M[(size_t)i * N + i] -= cf * ih2;
-                    }
-                const int pa[3] = {0, 0, 1}, pb[3] = {1, 2, 2};
-                for (int k = 0; k < 3; ++k) {
-                    const int a = pa[k], b = pb[k], comp = 3 + k;
-                    for (int sa = -1; sa <= 1; sa += 2)
-                        for (int sb = -1; sb <= 1; sb += 2) {
-                            int qa[3] = {p[0], p[1], p[2]}, qb[3] = {p[0], p[1], p[2]}, q[3] = {p[0], p[1], p[2]};
-                            qa[a] += sa;
-                            qb[b] += sb;
-                            q[a] += sa;
-                            q[b] += sb;
-                            const double v = sa * sb * (cc(comp, qa[0], qa[1], qa[2]) + cc(comp, qb[0], qb[1], qb[2])) * 0.25 * ih2;
-                            M[(size_t)i * N + id(q[0], q[1], q[2])] += v;
-                        }
-                }
-            }
-}
+// Carves a context's fields out of one block of device memory; with a null
+// base it only adds up the sizes.
+struct Arena {
+    char* base;
+    size_t used = 0;
+    void* take(size_t bytes) {
+        const size_t at = used;
+        used += (bytes + 255) & ~(size_t)255;
+        return base ? base + at : nullptr;
+    }
+    double* doubles(size_t count) { return (double*)take(count * sizeof(double)); }
+};
 
-// Zero-mean pseudo-inverse of a symmetric semidefinite M with null space span(1):
-// B = M - s 11^T / N is definite, and G = P B^-1 P with P = I - 11^T / N.
-bool pseudo_inverse(int N, const std::vector<double>& M, std::vector<double>& G) {
-    double s = 0.0;
-    for (int i = 0; i < N; ++i) s += std::fabs(M[(size_t)i * N + i]);
-    s /= N;
-    std::vector<double> A((size_t)N * 2 * N, 0.0);
-    for (int i = 0; i < N; ++i) {
-        for (int j = 0; j < N; ++j) A[(size_t)i * 2 * N + j] = M[(size_t)i * N + j] - s / N;
-        A[(size_t)i * 2 * N + N + i] = 1.0;
+// Pinned host mirrors, kHostDoubles each, handed out in pages that are kept and
+// reused: a pinned allocation costs more than a small solve.  Portable, so a
+// slot serves a context on any device.
+constexpr size_t kHostDoubles = 128, kPageSlots = 8;
+std::mutex g_host_mutex;
+std::vector<double*> g_host_free;
+hipError_t host_slot(double** out) {
+    std::lock_guard<std::mutex> lock(g_host_mutex);
+    if (g_host_free.empty()) {
+        g_host_free.reserve(kPageSlots);
+        double* page = nullptr;
+        // coherent: the finalize kernels write the outer sums into it directly
+        const hipError_t e = hipHostMalloc((void**)&page, kPageSlots * kHostDoubles * sizeof(double),
+                                           hipHostMallocCoherent | hipHostMallocPortable);
+        if (e != hipSuccess) return e;
+        for (size_t k = 0; k < kPageSlots; ++k) g_host_free.push_back(page + k * kHostDoubles);
     }
-    const int W = 2 * N;
-    for (int col = 0; col < N; ++col) {  // Gauss-Jordan with partial pivoting
-        int piv = col;
-        for (int r = col + 1; r < N; ++r)
-            if (std::fabs(A[(size_t)r * W + col]) > std::fabs(A[(size_t)piv * W + col])) piv = r;
-        if (A[(size_t)piv * W + col] == 0.0) return false;
-        if (piv != col)
-            for (int j = 0; j < W; ++j) std::swap(A[(size_t)piv * W + j], A[(size_t)col * W + j]);
-        const double inv = 1.0 / A[(size_t)col * W + col];
-        for (int j = 0; j < W; ++j) A[(size_t)col * W + j] *= inv;
-        for (int r = 0; r < N; ++r) {
-            if (r == col) continue;
-            const double f = A[(size_t)r * W + col];
-            if (f == 0.0) continue;
-            for (int j = 0; j < W; ++j) A[(size_t)r * W + j] -= f * A[(size_t)col * W + j];
-        }
+    *out = g_host_free.back();
+    g_host_free.pop_back();
+    return hipSuccess;
+}
+void host_slot_back(double* p) {
+    std::lock_guard<std::mutex> lock(g_host_mutex);
+    try {
+        g_host_free.push_back(p);
+    } catch (...) {  // no room to remember it: the slot is lost until the process ends
     }
-    std::vector<double> Bi((size_t)N * N);
-    for (int i = 0; i < N; ++i)
-        for (int j = 0; j < N; ++j) Bi[(size_t)i * N + j] = A[(size_t)i * W + N + j];
-    // G = P Bi P
-    std::vector<double> rm(N, 0.0), cm(N, 0.0);
-    double tm = 0.0;
-    for (int i = 0; i < N; ++i)
-        for (int j = 0; j < N; ++j) {
-            rm[i] += Bi[(size_t)i * N + j] / N;
-            cm[j] += Bi[(size_t)i * N + j] / N;
-        }
-    for (int i = 0; i < N; ++i) tm += rm[i] / N;
-    G.assign((size_t)N * N, 0.0);
-    for (int i = 0; i < N; ++i)
-        for (int j = 0; j < N; ++j) G[(size_t)i * N + j] = Bi[(size_t)i * N + j] - rm[i] - cm[j] + tm;
-    return true;
 }
 
 template <typename T>
@@ -985,21 +953,8 @@ mg_status mg_destroy(mg_ctx* c) {
     if (!c) return MG_OK;
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     else (void)hipDeviceSynchronize();
-    for (auto& L : c->lev) {
-        dfree(L.x[0]);
-        dfree(L.x[1]);
-        dfree(L.x[2]);
-        dfree(L.b);
-        dfree(L.coeff);
-    }
-    if (c->coeff_outer_owned) dfree(c->coeff_outer);
-    dfree(c->phi_tmp);
-    dfree(c->partials);
-    dfree(c->dscal);
-    if (c->hscal) (void)hipHostFree(c->hscal);
-    dfree(c->Q);
-    dfree(c->lam1);
-    dfree(c->G);
+    dfree(c->mem);
+    if (c->hscal) host_slot_back(c->hscal);
     dfree(c->scratch);
     dfree(c->pcg_r);
     dfree(c->pcg_p[0]);
@@ -1019,19 +974,25 @@ mg_status mg_destroy(mg_ctx* c) {
     return MG_OK;
 }
 
-static mg_status create_impl(mg_ctx* c, const void* coeff, int coeff_dtype, const double* psi = nullptr) {
+}  // extern "C"
+
+namespace {
+
+// What the hierarchy is built from.
+bool var_source(int source) { return source != MG_SOURCE_FLAT; }
+
+// Device memory that only the setup uses.
+struct SetupMem {
+    double* c64[12] = {};  // coefficients of each level in double, where the level itself does not keep them
+    double* psi[12] = {};  // restricted deformation potentials
+    double* dense = nullptr;
+};
+
+// Places every field of the context in `keep` and every temporary of its
+// setup in `tmp` (sizes only when their bases are null).
+void layout(mg_ctx* c, int source, Arena& keep, Arena& tmp, SetupMem& sm) {
     const mg_params& p = c->p;
-    c->var = coeff != nullptr || psi != nullptr;
-    c->inner_double = p.precision == MG_FP64;
-    if (c->var && coarsest_n(p) > 8)
-        return fail(c, MG_ERR_INVALID, "variable-coefficient coarsest level must have at most 8^3 points");
     const size_t Tsz = c->inner_double ? sizeof(double) : sizeof(float);
-    // reference switches of this context (mg_params.options)
-    c->use_pairs = (p.options & MG_OPT_NO_PAIR) == 0;
-    c->use_visits = (p.options & MG_OPT_NO_VISIT) == 0;
-    c->fuse_sums = (p.options & MG_OPT_NO_FUSED_SUMS) == 0;
-    c->use_tail = (p.options & MG_OPT_NO_TAIL) == 0;
-    c->use_graph = (p.options & MG_OPT_GRAPH) != 0;
     c->lev.resize(p.levels);
     for (int l = 0; l < p.levels; ++l) {
         Level& L = c->lev[l];
@@ -1039,198 +1000,258 @@ static mg_status create_impl(mg_ctx* c, const void* coeff, int coeff_dtype, cons
         L.N = (size_t)L.n * L.n * L.n;
         L.h = p.h * (double)(1 << l);
         L.ih2 = 1.0 / (L.h * L.h);
-        mg_status st;
-        if ((st = dalloc(c, &L.x[0], L.N * Tsz)) != MG_OK) return st;
-        if ((st = dalloc(c, &L.x[1], L.N * Tsz)) != MG_OK) return st;
+        L.x[0] = keep.take(L.N * Tsz);
+        L.x[1] = keep.take(L.N * Tsz);
         const bool third = c->use_pairs && (c->var ? var_pair_applies(L.n, Tsz) && p.smoother == MG_CHEBYSHEV &&
                                                          p.cheb_degree >= 2
                                                    : pair_kernels_apply(L.n, Tsz));
-        if (third && (st = dalloc(c, &L.x[2], L.N * Tsz)) != MG_OK) return st;
-        if ((st = dalloc(c, &L.b, L.N * Tsz)) != MG_OK) return st;
+        L.x[2] = third ? keep.take(L.N * Tsz) : nullptr;
+        L.b = keep.take(L.N * Tsz);
+        L.coeff = c->var ? keep.take(6 * L.N * Tsz) : nullptr;
     }
     const size_t N0 = c->lev[0].N;
-    mg_status st;
-    if ((st = dalloc(c, (void**)&c->phi_tmp, N0 * sizeof(double))) != MG_OK) return st;
-    // replaying the coarse sub-cycle from a HIP graph measured slower than eager
-    // launches on this platform; MG_OPT_GRAPH keeps it available
+    const int nc = c->lev.back().n;
+    const size_t Nc = c->lev.back().N;
+    c->phi_tmp = keep.doubles(N0);
     c->nparts = stencil_blocks(p.n);
     c->nparts_outer = outer_blocks(p.n, !c->var, p.precision != MG_FP32);
-    {
-        // three arrays: the outer kernels write three partial sums per block
-        const int np = c->nparts > c->nparts_outer ? c->nparts : c->nparts_outer;
-        if ((st = dalloc(c, (void**)&c->partials, 3 * (size_t)np * sizeof(double))) != MG_OK) return st;
+    // three arrays: the outer kernels write three partial sums per block
+    c->partials = keep.doubles(3 * (size_t)(c->nparts > c->nparts_outer ? c->nparts : c->nparts_outer));
+    c->dscal = keep.doubles(16);
+    if (!c->var) {
+        c->Q = keep.doubles((size_t)nc * nc);
+        c->lam1 = keep.doubles(nc);
+        return;
     }
-    if ((st = dalloc(c, (void**)&c->dscal, 16 * sizeof(double))) != MG_OK) return st;
-    // coherent: the finalize kernel writes the outer sums into it directly
-    HIPCHK(c, hipHostMalloc((void**)&c->hscal, 16 * sizeof(double), hipHostMallocCoherent));
-    HIPCHK(c, hipEventCreateWithFlags(&c->norm_ev, hipEventDisableTiming));
-    c->hscal[kHostFlagSlot] = 0.0;
-    c->hscal[kHostMeanSlot] = 0.0;
+    c->slots = (u64*)keep.take(kSetupSlots * sizeof(u64));
+    c->G = keep.doubles(Nc * Nc);
+    // the outer residual of a mixed solve uses the coefficients in double where they came in double
+    c->coeff_outer_double = c->inner_double || (p.precision == MG_MIXED && source != MG_SOURCE_COEFF_F32);
+    if (c->coeff_outer_double && !c->inner_double) c->coeff_outer = keep.take(6 * N0 * sizeof(double));
+    else c->coeff_outer = c->lev[0].coeff;
+    for (int l = 0; l < p.levels; ++l) {
+        const size_t N = c->lev[l].N;
+        if (c->inner_double) sm.c64[l] = (double*)c->lev[l].coeff;
+        else if (l == 0 && c->coeff_outer_double) sm.c64[l] = (double*)c->coeff_outer;
+        else if (l > 0 || source == MG_SOURCE_PSI || p.levels == 1) sm.c64[l] = tmp.doubles(6 * N);
+        if (source == MG_SOURCE_PSI && l > 0) sm.psi[l] = tmp.doubles(N);
+    }
+    sm.dense = tmp.doubles(dense_work(nc));
+}
 
-    if (c->var) {
-        // fine coefficients in double, validated, restricted level by level
-        std::vector<double*> c64(p.levels, nullptr);
-        auto free64 = [&]() {
-            for (auto q : c64) dfree(q);
-        };
-        for (int l = 0; l < p.levels; ++l)
-            if ((st = dalloc(c, (void**)&c64[l], 6 * c->lev[l].N * sizeof(double))) != MG_OK) {
-                free64();
-                return st;
+// Coefficients of every level, their checks and bounds, the coarsest inverse:
+// all enqueued, then one readback.
+mg_status setup_var(mg_ctx* c, int source, const void* field, const SetupMem& sm) {
+    const mg_params& p = c->p;
+    hipStream_t s = c->stream;
+    const int levels = p.levels;
+    u64* lmax = c->slots;
+    u64* bad = c->slots + 16;
+    HIPCHK(c, launch_clear_slots(c->slots, kSetupSlots, s));
+    auto inner_copy = [&](int l) { return c->inner_double ? nullptr : (float*)c->lev[l].coeff; };
+    if (source == MG_SOURCE_PSI) {
+        const double* psi = (const double*)field;
+        for (int l = 0; l < levels; ++l) {
+            const Level& L = c->lev[l];
+            if (l > 0) {
+                HIPCHK(c, launch_restrict_fields<double>(c->lev[l - 1].n, psi, sm.psi[l], nullptr, 1, s));
+                psi = sm.psi[l];
             }
-        // count of invalid cells of level l into hscal[0]
-        auto check_level = [&](int l) -> hipError_t {
-            hipError_t e = launch_coeff_check<double>(c->lev[l].n, c64[l], c->partials, c->stream);
-            if (e == hipSuccess) e = launch_finalize_sum(c->partials, stencil_blocks(c->lev[l].n), c->dscal, 0, c->stream);
-            if (e == hipSuccess) e = hipMemcpyAsync(c->hscal, c->dscal, sizeof(double), hipMemcpyDeviceToHost, c->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-            return e;
-        };
-        hipError_t e = hipSuccess;
-        if (psi) {
-            // every level rediscretised from the potential restricted to it
-            std::vector<double*> pl(p.levels, nullptr);
-            auto freep = [&]() {
-                for (int l = 1; l < p.levels; ++l) dfree(pl[l]);
-            };
-            pl[0] = const_cast<double*>(psi);
-            for (int l = 1; l < p.levels; ++l)
-                if ((st = dalloc(c, (void**)&pl[l], c->lev[l].N * sizeof(double))) != MG_OK) {
-                    freep();
-                    free64();
-                    return st;
-                }
-            for (int l = 0; l < p.levels && e == hipSuccess; ++l) {
-                if (l > 0) e = launch_restrict<double>(c->lev[l - 1].n, pl[l - 1], pl[l], 1, c->stream);
-                if (e == hipSuccess) e = launch_geometry<double>(c->lev[l].n, c->lev[l].ih2, pl[l], c64[l], nullptr, c->stream);
-            }
-            if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-            freep();
-            if (e != hipSuccess) { free64(); HIPCHK(c, e); }
-            for (int l = 0; l < p.levels; ++l) {
-                if ((e = check_level(l)) != hipSuccess) { free64(); HIPCHK(c, e); }
-                if (c->hscal[0] != 0.0) {
-                    free64();
-                    return fail(c, MG_ERR_INVALID_COEFF,
-                                std::to_string((long long)c->hscal[0]) + " cells of level " + std::to_string(l) +
-                                    " with a folded mesh (non-finite or non-positive diagonal coefficients)");
-                }
-            }
-        } else {
-            e = coeff_dtype == MG_DTYPE_F64
-                    ? launch_convert<double, double>(6 * N0, (const double*)coeff, c64[0], c->stream)
-                    : launch_convert<double, float>(6 * N0, (const float*)coeff, c64[0], c->stream);
-            if (e == hipSuccess) e = check_level(0);
-            if (e != hipSuccess) { free64(); HIPCHK(c, e); }
-            if (c->hscal[0] != 0.0) {
-                free64();
-                return fail(c, MG_ERR_INVALID_COEFF,
-                            std::to_string((long long)c->hscal[0]) + " cells with non-finite or non-positive diagonal coefficients");
-            }
-            for (int l = 0; l + 1 < p.levels; ++l) {
-                e = launch_restrict<double>(c->lev[l].n, c64[l], c64[l + 1], 6, c->stream);
-                if (e != hipSuccess) { free64(); HIPCHK(c, e); }
-            }
-        }
-        for (int l = 0; l + 1 < p.levels; ++l) {
-            OpDesc<double> op{c->lev[l].n, c->lev[l].ih2, c64[l]};
-            e = launch_gershgorin<double>(op, c->partials, c->stream);
-            if (e == hipSuccess) e = launch_finalize_max(c->partials, stencil_blocks(c->lev[l].n), c->dscal, 0, c->stream);
-            if (e != hipSuccess) { free64(); HIPCHK(c, e); }
-            if ((st = read_scalars(c, 1)) != MG_OK) { free64(); return st; }
-            c->lev[l].lmax = c->hscal[0];
-        }
-        // coarsest dense pseudo-inverse (host, double)
-        {
-            Level& Lc = c->lev.back();
-            std::vector<double> hc(6 * Lc.N), M, G;
-            e = hipMemcpyAsync(hc.data(), c64.back(), hc.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-            if (e != hipSuccess) { free64(); HIPCHK(c, e); }
-            assemble_dense(Lc.n, Lc.ih2, hc, M);
-            if (!pseudo_inverse((int)Lc.N, M, G)) {
-                free64();
-                return fail(c, MG_ERR_INVALID_COEFF, "coarsest operator is singular beyond its constant null space");
-            }
-            if ((st = dalloc(c, (void**)&c->G, G.size() * sizeof(double))) != MG_OK) { free64(); return st; }
-            e = hipMemcpyAsync(c->G, G.data(), G.size() * sizeof(double), hipMemcpyHostToDevice, c->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-            if (e != hipSuccess) { free64(); HIPCHK(c, e); }
-        }
-        // level storage in inner precision; outer fine copy
-        if (c->inner_double) {
-            for (int l = 0; l < p.levels; ++l) {
-                c->lev[l].coeff = c64[l];
-                c64[l] = nullptr;
-            }
-            c->coeff_outer = c->lev[0].coeff;
-            c->coeff_outer_double = true;
-            c->coeff_outer_owned = false;
-        } else {
-            for (int l = 0; l < p.levels; ++l) {
-                if ((st = dalloc(c, &c->lev[l].coeff, 6 * c->lev[l].N * sizeof(float))) != MG_OK) { free64(); return st; }
-                e = launch_convert<float, double>(6 * c->lev[l].N, c64[l], (float*)c->lev[l].coeff, c->stream);
-                if (e != hipSuccess) { free64(); HIPCHK(c, e); }
-            }
-            if (p.precision == MG_MIXED && (coeff_dtype == MG_DTYPE_F64 || psi)) {
-                c->coeff_outer = c64[0];  // keep the double values for the outer residual
-                c64[0] = nullptr;
-                c->coeff_outer_double = true;
-                c->coeff_outer_owned = true;
-            } else {
-                c->coeff_outer = c->lev[0].coeff;
-                c->coeff_outer_double = false;
-                c->coeff_outer_owned = false;
-            }
-        }
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        free64();
-        // levels of at most 16^3 points run in one kernel (coarsest 8^3 or 4^3)
-        const int steps = p.smoother == MG_JACOBI ? p.jacobi_sweeps : p.cheb_degree;
-        if (c->use_tail && steps <= kTailMaxSteps) {
-            int l0 = p.levels - 1;
-            while (l0 > 0 && c->lev[l0 - 1].n <= 16) --l0;
-            if (var_tail_applies(c->lev[l0].n, c->lev.back().n, p.levels - l0)) c->tail_start = l0;
+            HIPCHK(c, launch_geometry_fields(L.n, L.ih2, psi, sm.c64[l], inner_copy(l), nullptr, bad + l, s));
+            if (l + 1 < levels) HIPCHK(c, launch_bound<double>(L.n, sm.c64[l], lmax + l, s));
         }
     } else {
-        Level& Lc = c->lev.back();
-        std::vector<double> Q, lam;
-        flat_basis(Lc.n, Lc.h, Q, lam);
-        if ((st = dalloc(c, (void**)&c->Q, Q.size() * sizeof(double))) != MG_OK) return st;
-        if ((st = dalloc(c, (void**)&c->lam1, lam.size() * sizeof(double))) != MG_OK) return st;
-        HIPCHK(c, hipMemcpyAsync(c->Q, Q.data(), Q.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-        HIPCHK(c, hipMemcpyAsync(c->lam1, lam.data(), lam.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        c->coeff_outer = nullptr;
-        // levels of at most 16^3 points down to a coarsest of at most 8^3 run in one kernel
-        const int steps = p.smoother == MG_JACOBI ? p.jacobi_sweeps : p.cheb_degree;
-        if (Lc.n <= 8 && steps <= kTailMaxSteps && c->use_tail) {
-            int l0 = p.levels - 1;
-            while (l0 > 0 && c->lev[l0 - 1].n <= 16 && p.levels - (l0 - 1) <= kTailMaxLevels) --l0;
-            if (p.levels - l0 >= 2) c->tail_start = l0;
+        const Level& L0 = c->lev[0];
+        // the double copy of level 0 that the outer residual (or a one-level hierarchy) needs
+        double* outer = c->inner_double ? nullptr : sm.c64[0];
+        auto from = [&](auto* src) -> hipError_t {
+            typedef std::remove_const_t<std::remove_pointer_t<decltype(src)>> TS;
+            hipError_t e = c->inner_double ? launch_coeff_copy<TS, double>(L0.N, src, (double*)L0.coeff, outer, bad, s)
+                                           : launch_coeff_copy<TS, float>(L0.N, src, (float*)L0.coeff, outer, bad, s);
+            if (levels == 1 || e != hipSuccess) return e;
+            if ((e = launch_bound<TS>(L0.n, src, lmax, s)) != hipSuccess) return e;
+            return launch_restrict_fields<TS>(L0.n, src, sm.c64[1], inner_copy(1), 6, s);
+        };
+        HIPCHK(c, source == MG_SOURCE_COEFF_F64 ? from((const double*)field) : from((const float*)field));
+        for (int l = 1; l + 1 < levels; ++l) {
+            HIPCHK(c, launch_bound<double>(c->lev[l].n, sm.c64[l], lmax + l, s));
+            HIPCHK(c, launch_restrict_fields<double>(c->lev[l].n, sm.c64[l], sm.c64[l + 1], inner_copy(l + 1), 6, s));
         }
     }
-    for (auto& L : c->lev) make_schedule(p, L);
+    const Level& Lc = c->lev.back();
+    HIPCHK(c, launch_dense_inverse(Lc.n, Lc.ih2, sm.c64[levels - 1], c->G, sm.dense, bad + 16, s));
+    static_assert(16 + kSetupSlots <= kHostDoubles && sizeof(u64) == sizeof(double), "the slots fit the host mirror");
+    u64* host = reinterpret_cast<u64*>(c->hscal + 16);
+    HIPCHK(c, hipMemcpyAsync(host, c->slots, kSetupSlots * sizeof(u64), hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipStreamSynchronize(s));
+    for (int l = 0; l < levels; ++l) {
+        if (host[16 + l] == 0) continue;
+        const std::string cells = std::to_string((long long)host[16 + l]) + " cells ";
+        return fail(c, MG_ERR_INVALID_COEFF,
+                    source == MG_SOURCE_PSI
+                        ? cells + "of level " + std::to_string(l) +
+                              " with a folded mesh (non-finite or non-positive diagonal coefficients)"
+                        : cells + "with non-finite or non-positive diagonal coefficients");
+    }
+    if (host[32] != 0)
+        return fail(c, MG_ERR_INVALID_COEFF, "coarsest operator is singular beyond its constant null space");
+    for (int l = 0; l + 1 < levels; ++l) std::memcpy(&c->lev[l].lmax, &host[l], sizeof(double));
+    // levels of at most 16^3 points run in one kernel (coarsest 8^3 or 4^3)
+    const int steps = p.smoother == MG_JACOBI ? p.jacobi_sweeps : p.cheb_degree;
+    if (c->use_tail && steps <= kTailMaxSteps) {
+        int l0 = levels - 1;
+        while (l0 > 0 && c->lev[l0 - 1].n <= 16) --l0;
+        if (var_tail_applies(c->lev[l0].n, Lc.n, levels - l0)) c->tail_start = l0;
+    }
     return MG_OK;
 }
+
+mg_status setup_flat(mg_ctx* c) {
+    const mg_params& p = c->p;
+    Level& Lc = c->lev.back();
+    std::vector<double> Q, lam;
+    flat_basis(Lc.n, Lc.h, Q, lam);
+    HIPCHK(c, hipMemcpyAsync(c->Q, Q.data(), Q.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->lam1, lam.data(), lam.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    // levels of at most 16^3 points down to a coarsest of at most 8^3 run in one kernel
+    const int steps = p.smoother == MG_JACOBI ? p.jacobi_sweeps : p.cheb_degree;
+    if (Lc.n <= 8 && steps <= kTailMaxSteps && c->use_tail) {
+        int l0 = p.levels - 1;
+        while (l0 > 0 && c->lev[l0 - 1].n <= 16 && p.levels - (l0 - 1) <= kTailMaxLevels) --l0;
+        if (p.levels - l0 >= 2) c->tail_start = l0;
+    }
+    return MG_OK;
+}
+
+// Parameters the context's memory depends on.
+mg_status describe(mg_ctx* c, int source) {
+    const mg_params& p = c->p;
+    c->var = var_source(source);
+    c->inner_double = p.precision == MG_FP64;
+    if (c->var && coarsest_n(p) > 8)
+        return fail(c, MG_ERR_INVALID, "variable-coefficient coarsest level must have at most 8^3 points");
+    // reference switches of this context (mg_params.options)
+    c->use_pairs = (p.options & MG_OPT_NO_PAIR) == 0;
+    c->use_visits = (p.options & MG_OPT_NO_VISIT) == 0;
+    c->fuse_sums = (p.options & MG_OPT_NO_FUSED_SUMS) == 0;
+    c->use_tail = (p.options & MG_OPT_NO_TAIL) == 0;
+    // replaying the coarse sub-cycle from a HIP graph measured slower than eager
+    // launches on this platform; MG_OPT_GRAPH keeps it available
+    c->use_graph = (p.options & MG_OPT_GRAPH) != 0;
+    return MG_OK;
+}
+
+// keep / setup: the caller's memory, or null to allocate it here (one block
+// for the context, one for its setup, freed before the return).
+mg_status create_impl(mg_ctx* c, int source, const void* field, void* keep, size_t keep_bytes, void* setup,
+                      size_t setup_bytes) {
+    mg_status st = describe(c, source);
+    if (st != MG_OK) return st;
+    SetupMem sm;
+    Arena need_keep{nullptr}, need_tmp{nullptr};
+    layout(c, source, need_keep, need_tmp, sm);
+    void* own_tmp = nullptr;
+    if (keep) {
+        if (keep_bytes < need_keep.used || setup_bytes < need_tmp.used || (need_tmp.used && !setup))
+            return fail(c, MG_ERR_INVALID, "workspace too small");
+    } else {
+        if ((st = dalloc(c, &c->mem, need_keep.used)) != MG_OK) return st;
+        keep = c->mem;
+        if ((st = dalloc(c, &own_tmp, need_tmp.used)) != MG_OK) return st;
+        setup = own_tmp;
+    }
+    Arena A{(char*)keep}, B{(char*)setup};
+    layout(c, source, A, B, sm);
+    const hipError_t e = host_slot(&c->hscal);
+    if (e != hipSuccess) {
+        c->hscal = nullptr;
+        st = fail(c, MG_ERR_HIP, std::string("pinned host memory: ") + hipGetErrorString(e));
+    } else {
+        c->hscal[kHostFlagSlot] = 0.0;
+        c->hscal[kHostMeanSlot] = 0.0;
+        st = c->var ? setup_var(c, source, field, sm) : setup_flat(c);
+    }
+    if (own_tmp) {
+        (void)hipStreamSynchronize(c->stream);
+        dfree(own_tmp);
+    }
+    if (st != MG_OK) return st;
+    for (auto& L : c->lev) make_schedule(c->p, L);
+    return MG_OK;
+}
+
+mg_status create(const mg_params* p, int source, const void* field, void* keep, size_t keep_bytes, void* setup,
+                 size_t setup_bytes, void* stream, mg_ctx** out, const char* where) {
+    mg_ctx* c = new (std::nothrow) mg_ctx();
+    if (!c) return MG_ERR_NOMEM;
+    c->p = *p;
+    c->stream = (hipStream_t)stream;
+    mg_status st;
+    try {
+        st = create_impl(c, source, field, keep, keep_bytes, setup, setup_bytes);
+    } catch (const std::bad_alloc&) {
+        st = MG_ERR_NOMEM;
+    }
+    if (st != MG_OK) {
+        std::fprintf(stderr, "%s: %s\n", where, c->err.c_str());
+        mg_destroy(c);
+        return st;
+    }
+    *out = c;
+    return MG_OK;
+}
+
+bool valid_source(int source) { return source >= MG_SOURCE_FLAT && source <= MG_SOURCE_PSI; }
+
+}  // namespace
+
+extern "C" {
 
 mg_status mg_create(const mg_params* p, const void* coeff, int coeff_dtype, void* stream, mg_ctx** out) {
     if (!out) return MG_ERR_INVALID;
     *out = nullptr;
     if (mg_validate_params(p) != MG_OK) return MG_ERR_INVALID;
     if (coeff && coeff_dtype != MG_DTYPE_F32 && coeff_dtype != MG_DTYPE_F64) return MG_ERR_INVALID;
-    mg_ctx* c = new (std::nothrow) mg_ctx();
-    if (!c) return MG_ERR_NOMEM;
-    c->p = *p;
-    c->stream = (hipStream_t)stream;
-    mg_status st = create_impl(c, coeff, coeff_dtype);
-    if (st != MG_OK) {
-        std::fprintf(stderr, "mg_create: %s\n", c->err.c_str());
-        mg_destroy(c);
-        return st;
+    const int source = !coeff                          ? MG_SOURCE_FLAT
+                       : coeff_dtype == MG_DTYPE_F32 ? MG_SOURCE_COEFF_F32
+                                                       : MG_SOURCE_COEFF_F64;
+    return create(p, source, coeff, nullptr, 0, nullptr, 0, stream, out, "mg_create");
+}
+
+mg_status mg_create_psi(const mg_params* p, const double* psi, void* stream, mg_ctx** out) {
+    if (!out) return MG_ERR_INVALID;
+    *out = nullptr;
+    if (!psi || mg_validate_params(p) != MG_OK) return MG_ERR_INVALID;
+    return create(p, MG_SOURCE_PSI, psi, nullptr, 0, nullptr, 0, stream, out, "mg_create_psi");
+}
+
+mg_status mg_workspace_bytes(const mg_params* p, int source, size_t* keep_bytes, size_t* setup_bytes) {
+    if (!keep_bytes || !setup_bytes || !valid_source(source) || mg_validate_params(p) != MG_OK) return MG_ERR_INVALID;
+    try {
+        mg_ctx c;
+        c.p = *p;
+        const mg_status st = describe(&c, source);
+        if (st != MG_OK) return st;
+        SetupMem sm;
+        Arena A{nullptr}, B{nullptr};
+        layout(&c, source, A, B, sm);
+        *keep_bytes = A.used;
+        *setup_bytes = B.used;
+    } catch (const std::bad_alloc&) {
+        return MG_ERR_NOMEM;
     }
-    *out = c;
     return MG_OK;
+}
+
+mg_status mg_create_in(const mg_params* p, int source, const void* field, void* keep, size_t keep_bytes, void* setup,
+                       size_t setup_bytes, void* stream, mg_ctx** out) {
+    if (!out) return MG_ERR_INVALID;
+    *out = nullptr;
+    if (!valid_source(source) || mg_validate_params(p) != MG_OK || !keep || ((uintptr_t)keep & 15) != 0 ||
+        ((uintptr_t)setup & 15) != 0 || var_source(source) != (field != nullptr))
+        return MG_ERR_INVALID;
+    return create(p, source, field, keep, keep_bytes, setup, setup_bytes, stream, out, "mg_create_in");
 }
 
 mg_status mg_set_stream(mg_ctx* c, void* stream) {
@@ -1482,6 +1503,7 @@ mg_status mg_cycles(mg_ctx* c, double* phi, const double* b, int cycles, double*
 namespace {
 
 mg_status ensure_pcg(mg_ctx* c) {
+    if (!c->norm_ev) HIPCHK(c, hipEventCreateWithFlags(&c->norm_ev, hipEventDisableTiming));
     if (c->pcg_r) return MG_OK;
     const size_t bytes = c->lev[0].N * sizeof(double);
     mg_status st;
@@ -1638,24 +1660,6 @@ mg_status mg_solve_pcg(mg_ctx* c, double* phi, const double* b, double tol, int 
               : pcg_impl<float, float>(c, phi, b, tol, max_iter, info);
 }
 
-mg_status mg_create_psi(const mg_params* p, const double* psi, void* stream, mg_ctx** out) {
-    if (!out) return MG_ERR_INVALID;
-    *out = nullptr;
-    if (!psi || mg_validate_params(p) != MG_OK) return MG_ERR_INVALID;
-    mg_ctx* c = new (std::nothrow) mg_ctx();
-    if (!c) return MG_ERR_NOMEM;
-    c->p = *p;
-    c->stream = (hipStream_t)stream;
-    mg_status st = create_impl(c, nullptr, MG_DTYPE_F64, psi);
-    if (st != MG_OK) {
-        std::fprintf(stderr, "mg_create_psi: %s\n", c->err.c_str());
-        mg_destroy(c);
-        return st;
-    }
-    *out = c;
-    return MG_OK;
-}
-
 mg_status mg_predict(int n, int kind, const double* phi1, const double* phi2, const double* phi3, double growth,
                      double* out, void* stream) {
     if (!is_pow2(n) || n < 4 || n > 2048 || !phi1 || !out) return MG_ERR_INVALID;
@@ -1732,9 +1736,13 @@ mg_status mg_geometry(int n, double h, const double* psi, void* C_out, int dtype
     if (!is_pow2(n) || n < 4 || n > 2048 || !(h > 0) || !psi || !C_out) return MG_ERR_INVALID;
     const double ih2 = 1.0 / (h * h);
     hipError_t e;
-    if (dtype == MG_DTYPE_F64) e = launch_geometry<double>(n, ih2, psi, (double*)C_out, sqrtg_out, (hipStream_t)stream);
-    else if (dtype == MG_DTYPE_F32) e = launch_geometry<float>(n, ih2, psi, (float*)C_out, sqrtg_out, (hipStream_t)stream);
-    else return MG_ERR_INVALID;
+    hipStream_t s = (hipStream_t)stream;
+    if (dtype == MG_DTYPE_F64)
+        e = launch_geometry_fields(n, ih2, psi, (double*)C_out, nullptr, sqrtg_out, nullptr, s);
+    else if (dtype == MG_DTYPE_F32)
+        e = launch_geometry_fields(n, ih2, psi, nullptr, (float*)C_out, sqrtg_out, nullptr, s);
+    else
+        return MG_ERR_INVALID;
     return e == hipSuccess ? MG_OK : MG_ERR_HIP;
 }
 

@@ -41,20 +41,6 @@ __device__ double block_sum(double v, double* sh) {
     __syncthreads();
     return r;
 }
-__device__ double block_max(double v, double* sh) {
-    const int tid = lin_tid();
-    const int nt = blockDim.x * blockDim.y * blockDim.z;
-    sh[tid] = v;
-    __syncthreads();
-    for (int s = nt >> 1; s > 0; s >>= 1) {
-        if (tid < s) sh[tid] = fmax(sh[tid], sh[tid + s]);
-        __syncthreads();
-    }
-    double r = sh[0];
-    __syncthreads();
-    return r;
-}
-
 // ---- field accessors (value of the iterate at a linear index, in type T) ----
 template <typename T, typename TU>
 struct Plain {
