@@ -13,9 +13,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libmg.so")
 OBJDIR = os.path.join(ROOT, "_build")
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("flat_row.hip", "var_row.hip", "kernels.hip", "tail.hip",
-                                                    "var_tail.hip", "var_visit.hip", "visit.hip", "setup.hip",
-                                                    "pcg.hip", "readout.hip", "noalloc.hip", "mg_api.cpp")]
+SOURCES = [os.path.join(HERE, "csrc", f)
+           for f in ("flat_row.hip", "pair_tile.hip", "var_row.hip", "kernels.hip", "tail.hip", "var_tail.hip",
+                     "var_visit.hip", "visit.hip", "setup.hip", "pcg.hip", "readout.hip", "noalloc.hip", "mg_api.cpp")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
