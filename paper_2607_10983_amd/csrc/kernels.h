@@ -163,7 +163,6 @@ hipError_t launch_pcg_update(int n, double* phi, const double* p, double* r, con
 //   kPcgBeta:  rz_new = sum r z; beta = restart ? 0 : -alpha (sum z q) / rz_old (flexible,
 //              Polak-Ribiere form); scal[kPcgRz] = rz_new
 //   kPcgAlpha: alpha = scal[kPcgRz] / sum p q
-//   kPcgRr:    scal[kPcgRr] = sum r^2
 hipError_t launch_pcg_scalars(const double* partials, int nb, double* scal, int which, bool restart,
                               hipStream_t s);
 

@@ -20,6 +20,7 @@
 
 #include "flat_row.h"
 #include "kernels.h"
+#include "pcg_row.h"
 #include "setup.h"
 #include "tail.h"
 #include "var_row.h"
@@ -1447,17 +1448,26 @@ mg_status mg_cycles(mg_ctx* c, double* phi, const double* b, int cycles, double*
 
 namespace {
 
+// The seven-point passes on rows form q = M p where they use it, and a double
+// hierarchy's right-hand side serves as r.
+inline bool pcg_rows(const mg_ctx* c) { return !c->var && pcg_row_applies(c->lev[0].n); }
+
 mg_status ensure_pcg(mg_ctx* c) {
     if (!c->norm_ev) HIPCHK(c, hipEventCreateWithFlags(&c->norm_ev, hipEventDisableTiming));
-    if (c->pcg_r) return MG_OK;
+    const int n = c->lev[0].n;
     const size_t bytes = c->lev[0].N * sizeof(double);
-    mg_status st;
-    if ((st = dalloc(c, (void**)&c->pcg_r, bytes)) != MG_OK) return st;
-    if ((st = dalloc(c, (void**)&c->pcg_p[0], bytes)) != MG_OK) return st;
-    if ((st = dalloc(c, (void**)&c->pcg_p[1], bytes)) != MG_OK) return st;
-    if ((st = dalloc(c, (void**)&c->pcg_q, bytes)) != MG_OK) return st;
-    if ((st = dalloc(c, (void**)&c->pcg_s, kPcgSlots * sizeof(double))) != MG_OK) return st;
-    return dalloc(c, (void**)&c->pcg_partials, 2 * (size_t)pcg_blocks(c->lev[0].n) * sizeof(double));
+    const size_t parts = pcg_rows(c) ? 3 * (size_t)pcg_row_blocks(n) : 2 * (size_t)pcg_blocks(n);
+    mg_status st = MG_OK;
+    auto need = [&](double*& p, size_t size) {
+        if (st == MG_OK && !p) st = dalloc(c, (void**)&p, size);
+    };
+    if (!c->inner_double) need(c->pcg_r, bytes);
+    need(c->pcg_p[0], bytes);
+    need(c->pcg_p[1], bytes);
+    if (!pcg_rows(c)) need(c->pcg_q, bytes);
+    need(c->pcg_s, kPcgSlots * sizeof(double));
+    need(c->pcg_partials, parts * sizeof(double));
+    return st;
 }
 
 // Multigrid-preconditioned CG.  TI: type of the hierarchy (preconditioner
@@ -1471,28 +1481,46 @@ mg_status pcg_impl(mg_ctx* c, double* phi, const double* b, double tol, int max_
     const double invN = 1.0 / (double)N0;
     const OpDesc<TC> op{n, L0.ih2, (const TC*)c->coeff_outer};
     TI* rin = (TI*)L0.b;
-    double* r = c->pcg_r;
+    double* r = c->inner_double ? (double*)L0.b : c->pcg_r;
     double* q = c->pcg_q;
     double* S = c->pcg_s;
     double* part = c->pcg_partials;
-    const int nb = pcg_blocks(n);
+    const bool rows = pcg_rows(c);
+    const int nb = rows ? pcg_row_blocks(n) : pcg_blocks(n);
     mg_status st;
     c->x1_ready = false;
     c->pending_sums = false;
-    if ((st = device_sum(c, b, 0.0, 1, 0)) != MG_OK) return st;
-    if ((st = read_scalars(c, 1)) != MG_OK) return st;
-    const double bmean = c->hscal[0] * invN;
-    if (!std::isfinite(bmean)) return fail(c, MG_ERR_NONFINITE, "source contains NaN or Inf");
-    if ((st = device_sum(c, b, bmean, 2, 1)) != MG_OK) return st;
+    if ((st = device_sum(c, b, 0.0, 1, 0, true)) != MG_OK) return st;
+    double bmean = 0.0;
+    if (!rows) {  // the row passes read the sum on the device
+        if ((st = wait_mean(c)) != MG_OK) return st;
+        bmean = c->hscal[0] * invN;
+        if (!std::isfinite(bmean)) return fail(c, MG_ERR_NONFINITE, "source contains NaN or Inf");
+        if ((st = device_sum(c, b, bmean, 2, 1)) != MG_OK) return st;
+    }
+    // r, r_in and the sums of slots 1 .. 3 on their way to the host (slot 3, of phi, from the row passes)
     auto true_residual = [&]() -> mg_status {
+        if (rows) {
+            HIPCHK(c, launch_pcg_row_residual<TI>(n, L0.ih2, phi, b, Mean{c->dscal, invN}, r, rin, part, c->stream));
+            c->sums_seq += 1.0;
+            c->scal_flag = true;
+            HIPCHK(c, launch_finalize_sums(part, nb, 3, c->dscal, 1, c->stream, c->hscal, c->sums_seq));
+            return MG_OK;
+        }
         HIPCHK(c, (launch_pcg_residual<TI, TC>(op, phi, b, bmean, r, rin, part, c->stream)));
         HIPCHK(c, launch_finalize_sum(part, nb, c->dscal, 2, c->stream));
-        return MG_OK;
+        return post_scalars(c, 3);
     };
     if ((st = true_residual()) != MG_OK) return st;
-    if ((st = post_scalars(c, 3)) != MG_OK) return st;
     bool ahead = max_iter > 0;  // look-ahead preconditioner application, as in the defect-correction loop
     if (ahead && (st = inner_vcycle(c)) != MG_OK) return st;
+    if (rows) {
+        if ((st = wait_mean(c)) != MG_OK) return st;
+        if (!std::isfinite(c->hscal[0] * invN)) {
+            (void)hipStreamSynchronize(c->stream);
+            return fail(c, MG_ERR_NONFINITE, "source contains NaN or Inf");
+        }
+    }
     if ((st = wait_scalars(c)) != MG_OK) return st;
     const double nbn = std::sqrt(c->hscal[1]);
     if (info) {
@@ -1524,23 +1552,31 @@ mg_status pcg_impl(mg_ctx* c, double* phi, const double* b, double tol, int max_
         const TI* z = (const TI*)inner_e(c);
         double* p_old = c->pcg_p[pc];
         double* p_new = c->pcg_p[1 - pc];
-        HIPCHK(c, launch_pcg_dots<TI>(n, r, z, restart ? nullptr : q, part, c->stream));
-        HIPCHK(c, launch_pcg_scalars(part, nb, S, kPcgBeta, restart, c->stream));
-        HIPCHK(c, (launch_pcg_direction<TI, TC>(op, z, p_old, p_new, q, S, restart, part, c->stream)));
-        HIPCHK(c, launch_pcg_scalars(part, nb, S, kPcgAlpha, false, c->stream));
-        HIPCHK(c, launch_pcg_update<TI>(n, phi, p_new, r, q, rin, S, part, c->stream));
-        HIPCHK(c, launch_pcg_scalars(part, nb, S, kPcgRr, false, c->stream));
+        if (rows) {
+            const double* p_prev = restart ? nullptr : p_old;
+            HIPCHK(c, launch_pcg_row_dots<TI>(n, L0.ih2, r, z, p_prev, part, c->stream));
+            HIPCHK(c, launch_pcg_scalars(part, nb, S, kPcgBeta, restart, c->stream));
+            HIPCHK(c, launch_pcg_row_direction<TI>(n, L0.ih2, z, p_prev, p_new, S, part, c->stream));
+            HIPCHK(c, launch_pcg_scalars(part, nb, S, kPcgAlpha, false, c->stream));
+            HIPCHK(c, launch_pcg_row_update<TI>(n, L0.ih2, phi, p_new, r, rin, S, part, c->stream));
+        } else {
+            HIPCHK(c, launch_pcg_dots<TI>(n, r, z, restart ? nullptr : q, part, c->stream));
+            HIPCHK(c, launch_pcg_scalars(part, nb, S, kPcgBeta, restart, c->stream));
+            HIPCHK(c, (launch_pcg_direction<TI, TC>(op, z, p_old, p_new, q, S, restart, part, c->stream)));
+            HIPCHK(c, launch_pcg_scalars(part, nb, S, kPcgAlpha, false, c->stream));
+            HIPCHK(c, launch_pcg_update<TI>(n, phi, p_new, r, q, rin, S, part, c->stream));
+        }
+        c->sums_seq += 1.0;
+        c->scal_flag = true;
+        HIPCHK(c, launch_finalize_sums(part, nb, 1, S, kPcgRr, c->stream, c->hscal, c->sums_seq));
         pc = 1 - pc;
         restart = false;
         true_current = false;
-        HIPCHK(c, hipMemcpyAsync(c->hscal, S + kPcgRr, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipEventRecord(c->norm_ev, c->stream));
-        c->scal_flag = false;
         ahead = its + 1 < max_iter && rho * rel > tol;
         if (ahead && (st = inner_vcycle(c)) != MG_OK) return st;
         if ((st = wait_scalars(c)) != MG_OK) return st;
         const double prev = rel;
-        rel = std::sqrt(c->hscal[0]) / nbn;
+        rel = std::sqrt(c->hscal[kPcgRr]) / nbn;
         ++its;
         if (prev > 0.0 && std::isfinite(rel)) rho = std::min(1.0, std::max(1e-3, rel / prev));
         if (info && info->history && its < info->history_cap) info->history[its] = rel;
@@ -1551,7 +1587,7 @@ mg_status pcg_impl(mg_ctx* c, double* phi, const double* b, double tol, int max_
         if (rel <= tol) {
             // the recursive residual met tol: confirm with the true residual
             if ((st = true_residual()) != MG_OK) return st;
-            if ((st = read_scalars(c, 3)) != MG_OK) return st;
+            if ((st = wait_scalars(c)) != MG_OK) return st;
             true_rel = std::sqrt(c->hscal[2]) / nbn;
             true_current = true;
             if (true_rel > tol && its < max_iter) {
@@ -1569,7 +1605,7 @@ mg_status pcg_impl(mg_ctx* c, double* phi, const double* b, double tol, int max_
     }
     if (!true_current && result == MG_OK) {
         if ((st = true_residual()) != MG_OK) return st;
-        if ((st = read_scalars(c, 3)) != MG_OK) return st;
+        if ((st = wait_scalars(c)) != MG_OK) return st;
         true_rel = std::sqrt(c->hscal[2]) / nbn;
     }
     if (result == MG_OK && true_rel > tol) {
@@ -1577,10 +1613,11 @@ mg_status pcg_impl(mg_ctx* c, double* phi, const double* b, double tol, int max_
         c->err = "relative residual " + std::to_string(true_rel) + " > tol after " + std::to_string(its) +
                  " iterations";
     }
-    // gauge: phi <- phi - mean(phi)
-    if ((st = device_sum(c, phi, 0.0, 1, 3)) != MG_OK) return st;
-    if ((st = read_scalars(c, 4)) != MG_OK) return st;
-    HIPCHK(c, launch_shift(N0, phi, c->hscal[3] * invN, phi, c->stream));
+    // gauge: phi <- phi - mean(phi), from the sum on the device
+    if (!rows || (!true_current && result != MG_OK)) {
+        if ((st = device_sum(c, phi, 0.0, 1, 3)) != MG_OK) return st;
+    }
+    HIPCHK(c, launch_gauge(N0, phi, c->dscal, invN, phi, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (info) {
         info->cycles = its;

@@ -11,9 +11,15 @@
 //   direction  p = z + beta p_prev, q = M p, (p, q)  reads z, p_prev; writes p, q
 //   scalars    alpha = rz / (p, q)
 //   update     phi += alpha p, r -= alpha q, r_in    reads phi, p, r, q; writes phi, r, r_in
-//   scalars    (r, r)
+//   sums       (r, r)
+//
+// With a double hierarchy r is the preconditioner's input itself (r_in is not
+// written).  The seven-point operator on rows of 64 points and more takes the
+// passes of pcg_row.hip, which do not store q.
 #include "kernels.h"
 #include "stencil.h"
+
+#include <type_traits>
 
 namespace mg {
 namespace {
@@ -48,7 +54,7 @@ __global__ __launch_bounds__(kThreads) void k_pcg_residual(int n, double ih2, co
         else var_Mu<double, TC>(u, C, N, g, x, y, z, uc, ih2, Mu, D);
         const double ri = (b[i] - bmean) - Mu;
         r[i] = ri;
-        rin[i] = (TI)ri;
+        if constexpr (!std::is_same<TI, double>::value) rin[i] = (TI)ri;
         ss += ri * ri;
     }
     const double tot = block_sum(ss, sh);
@@ -134,7 +140,7 @@ __global__ __launch_bounds__(kThreads) void k_pcg_update(int n, double* __restri
         phi[i] += alpha * p[i];
         const double ri = r[i] - alpha * q[i];
         r[i] = ri;
-        rin[i] = (TI)ri;
+        if constexpr (!std::is_same<TI, double>::value) rin[i] = (TI)ri;
         ss += ri * ri;
     }
     const double tot = block_sum(ss, sh);
@@ -158,11 +164,9 @@ __global__ __launch_bounds__(1024) void k_pcg_scalars(const double* __restrict__
         // r_k - r_{k-1} = -alpha_{k-1} q_{k-1}
         scal[kPcgBeta] = restart ? 0.0 : -scal[kPcgAlpha] * s1 / scal[kPcgRz];
         scal[kPcgRz] = s0;
-    } else if (which == kPcgAlpha) {
+    } else {
         scal[kPcgPq] = s0;
         scal[kPcgAlpha] = scal[kPcgRz] / s0;
-    } else {
-        scal[kPcgRr] = s0;
     }
 }
 
