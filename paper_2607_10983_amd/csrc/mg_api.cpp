@@ -104,7 +104,7 @@ struct mg_ctx {
     bool scal_flag = false;  // the pending readback is the flag, not norm_ev
     double mean_seq = 0.0;   // number of the last readback of the sum of b
     bool use_pairs = true;         // last two steps of a smoothing pass in one two-step kernel
-    bool use_visits = true;        // fused visits of the 32^3 and 64^3 levels (float hierarchy)
+    bool use_visits = true;        // fused visits of the 32^3 and 64^3 levels
     bool use_tail = true;          // levels of at most 16^3 points in one workgroup
     // conjugate-gradient state (allocated by the first mg_solve_pcg)
     double* pcg_r = nullptr;
@@ -304,11 +304,12 @@ inline bool x1_fusable(const mg_ctx* c) { return c->tail_start != 0 && c->lev.si
 // fused visit kernels: float hierarchy, seven-point operator, 32^3 or 64^3
 // points; pre (post) selects the visit before (after) the coarse correction.
 inline bool visit_level(const mg_ctx* c, int l, bool pre) {
-    if (!(c->use_visits && !c->var && !c->inner_double && c->p.smoother == MG_CHEBYSHEV &&
-          l + 1 < (int)c->lev.size() && l != c->tail_start))
+    if (!(c->use_visits && !c->var && c->p.smoother == MG_CHEBYSHEV && l + 1 < (int)c->lev.size() &&
+          l != c->tail_start))
         return false;
     const int n = c->lev[l].n, v = (int)c->lev[l].a.size();
-    return pre ? visit_pre_applies(n, v) : visit_post_applies(n, v);
+    const size_t elem = c->inner_double ? sizeof(double) : sizeof(float);
+    return pre ? visit_pre_applies(n, v, elem) : visit_post_applies(n, v, elem);
 }
 
 // 19-point levels of 32^3 points: pre- and post-visits in one launch each.
@@ -740,10 +741,10 @@ mg_status vcycle_from_zero(mg_ctx* c, int l) {
     Level& Lc = c->lev[l + 1];
     mg_status st = MG_OK;
     const int v = (int)L.a.size();
-    if (std::is_same<T, float>::value && visit_level(c, l, true)) {  // one launch before the coarse level
+    if (visit_level(c, l, true)) {  // one launch before the coarse level
         if (l == 0) c->x1_ready = false;
-        HIPCHK(c, launch_visit_pre(L.n, L.ih2, (const float*)L.b, (float*)L.x[0], (float*)Lc.b, L.a.data(),
-                                   L.c.data(), v, c->stream));
+        HIPCHK(c, launch_visit_pre<T>(L.n, L.ih2, (const T*)L.b, (T*)L.x[0], (T*)Lc.b, L.a.data(), L.c.data(), v,
+                                      c->stream));
         L.cur = 0;
     } else if (var_visit_level(c, l)) {
         if ((st = var_visit_pre<T>(c, l)) != MG_OK) return st;
@@ -752,10 +753,10 @@ mg_status vcycle_from_zero(mg_ctx* c, int l) {
         if ((st = residual_restrict_level<T>(c, l, true)) != MG_OK) return st;
     }
     if ((st = vcycle_from_zero<T>(c, l + 1)) != MG_OK) return st;
-    if (std::is_same<T, float>::value && visit_level(c, l, false)) {  // and one after it
+    if (visit_level(c, l, false)) {  // and one after it
         const int nx = other(L.cur);
-        HIPCHK(c, launch_visit_post(L.n, L.ih2, (const float*)L.x[L.cur], (const float*)Lc.x[Lc.cur],
-                                    (const float*)L.b, (float*)L.x[nx], L.a.data(), L.c.data(), v, c->stream));
+        HIPCHK(c, launch_visit_post<T>(L.n, L.ih2, (const T*)L.x[L.cur], (const T*)Lc.x[Lc.cur], (const T*)L.b,
+                                       (T*)L.x[nx], L.a.data(), L.c.data(), v, c->stream));
         L.cur = nx;
         return MG_OK;
     }

