@@ -3,246 +3,260 @@
 // Levels with at most 16^3 points are far too small to fill the chip; one
 // kernel launch per smoothing step there costs more in launch latency than in
 // work.  This kernel runs the whole remaining V-cycle from a small level down
-// to the coarsest and back up inside ONE workgroup of 1024 threads: every
-// smoothing step, residual, restriction, coarsest solve and prolongation is
-// a phase of the same kernel, separated by workgroup barriers.  All tail
-// level fields live in LDS (gfx950 gives a workgroup up to 160 KB: three
-// fields of 16^3 + 8^3 + 4^3 points take 56 KB in float, 112 KB in double);
-// only the first tail level's right-hand side is read from and its result
-// written back to global memory.  The coarsest level's exact solve
-// (separable real Fourier basis) also runs in LDS, in double.
+// to the coarsest and back up inside ONE workgroup of 1024 threads, its phases
+// separated by workgroup barriers.
+//
+// A phase is bound by the LDS and the barrier of one CU, so the fields stay in
+// registers: a thread owns 4 consecutive x points of the 16^3 level (x, x_prev
+// and b there) and one point of the 8^3 level, and publishes only the iterate
+// of each step, in two alternating copies (one barrier per step).  The x
+// neighbours of a 16^3 segment come from the other lanes of its quad.  The
+// residual is weighted in x before it is published, and the prolongation reads
+// its coarse rows without branches.  The coarsest level's exact solve
+// (separable real Fourier basis) runs in double, a 4^3 one inside one wave.
+//
+// Degree 3, 16^3 to 4^3: 8.7 us per launch in float and 11.7 in double, against
+// 19 and 25.8 with every field in LDS and each point reading its neighbours, b
+// and x_prev from there.
 #include "tail.h"
+
+#include "row.h"
 
 namespace mg {
 namespace {
 
 constexpr int kTailThreads = 1024;
 
-// Level geometry as compile-time constants: the tail's levels have 16^3, 8^3
-// or 4^3 points, and with the sizes fixed every neighbour index reduces to a
-// few masks and the per-thread point loops unroll.
-template <int N>
-struct Geo {
-    static constexpr int n = N;
-    static constexpr int lg = N == 16 ? 4 : N == 8 ? 3 : 2;
-    static constexpr int P = N * N * N;
-    static constexpr int m = N - 1;
-    static constexpr int pts = (P + kTailThreads - 1) / kTailThreads;  // points per thread
-    static_assert(N == 4 || N == 8 || N == 16, "tail levels have 4^3, 8^3 or 16^3 points");
-    __device__ static __forceinline__ void coords(int i, int& x, int& y, int& z) {
-        x = i & m;
-        y = (i >> lg) & m;
-        z = i >> (2 * lg);
-    }
-    __device__ static __forceinline__ int at(int x, int y, int z) {
-        return ((((z & m) << lg) | (y & m)) << lg) | (x & m);
-    }
-};
-
-template <typename T, int N>
-__device__ __forceinline__ T Mx_at(const T* u, int i, T ih2) {
-    using G = Geo<N>;
-    constexpr int mx = G::m, my = G::m << G::lg, pz = N * N;
-    const T c = u[i];
-    T s = u[(i & ~mx) | ((i - 1) & mx)] + u[(i & ~mx) | ((i + 1) & mx)];
-    s += u[(i & ~my) | ((i - N) & my)] + u[(i & ~my) | ((i + N) & my)];
-    s += u[(i - pz) & (G::P - 1)] + u[(i + pz) & (G::P - 1)];
-    return (s - T(6) * c) * ih2;
+// value of the next (+1) or previous (-1) lane of the quad, wrapping inside it
+template <int D>
+__device__ __forceinline__ int quad_rot32(int v) {
+    // quad_perm selectors [1,2,3,0] and [3,0,1,2]
+    return __builtin_amdgcn_update_dpp(0, v, D > 0 ? 0x39 : 0x93, 0xF, 0xF, false);
 }
-
-// Every phase computes the thread's points with all loads issued before any
-// store, then stores them, then waits at the barrier.
-template <typename T, int P, typename F>
-__device__ __forceinline__ void phase(F f, T* out) {
-    constexpr int K = (P + kTailThreads - 1) / kTailThreads;
-    T v[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int i = threadIdx.x + k * kTailThreads;
-        if (P % kTailThreads == 0 || i < P) v[k] = f(i);
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int i = threadIdx.x + k * kTailThreads;
-        if (P % kTailThreads == 0 || i < P) out[i] = v[k];
-    }
-    __syncthreads();
-}
-
-// 16^3 stencil phases: thread t owns the 4 consecutive x points 4t .. 4t+3
-// (a quarter of an x row), so its own points and the y and z neighbour
-// segments come with one 16-byte LDS access each, and only the two x
-// neighbours beyond the segment are single loads: 7 LDS reads for 4 points
-// instead of 28.  Same expression as Mx_at, point by point.
-template <typename T>
-__device__ __forceinline__ void seg4(T (&v)[4], const T* p) {
+template <int D, typename T>
+__device__ __forceinline__ T quad_rot(T v) {
     if constexpr (sizeof(T) == 4) {
-        const float4 t = *reinterpret_cast<const float4*>(p);
-        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+        return __builtin_bit_cast(T, quad_rot32<D>(__builtin_bit_cast(int, v)));
     } else {
-        const double2 a = *reinterpret_cast<const double2*>(p);
-        const double2 b = *reinterpret_cast<const double2*>(p + 2);
-        v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+        v2i h = __builtin_bit_cast(v2i, v);
+        h.x = quad_rot32<D>(h.x);
+        h.y = quad_rot32<D>(h.y);
+        return __builtin_bit_cast(T, h);
     }
 }
+
+// A copy of the 16^3 level, segment i (points 4 i .. 4 i + 3) in 16-byte
+// pieces with piece j of all segments together, so that the lanes of a wave
+// access consecutive addresses in both types.
 template <typename T>
-__device__ __forceinline__ void put4(T* p, const T (&v)[4]) {
-    if constexpr (sizeof(T) == 4) {
-        *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-    } else {
-        *reinterpret_cast<double2*>(p) = make_double2(v[0], v[1]);
-        *reinterpret_cast<double2*>(p + 2) = make_double2(v[2], v[3]);
-    }
-}
-// M u at the 4 points i0 .. i0+3 of a 16^3 level (i0 a multiple of 4); c = u there
-template <typename T>
-__device__ __forceinline__ void Mx16_seg(const T* u, int i0, T ih2, T (&c)[4], T (&Mx)[4]) {
-    constexpr int N = 16, P = N * N * N, mx = N - 1, my = (N - 1) * N, pz = N * N;
-    T ym[4], yp[4], zm[4], zp[4];
-    seg4<T>(c, u + i0);
-    seg4<T>(ym, u + ((i0 & ~my) | ((i0 - N) & my)));
-    seg4<T>(yp, u + ((i0 & ~my) | ((i0 + N) & my)));
-    seg4<T>(zm, u + ((i0 - pz) & (P - 1)));
-    seg4<T>(zp, u + ((i0 + pz) & (P - 1)));
-    const T lft = u[(i0 & ~mx) | ((i0 - 1) & mx)];
-    const T rgt = u[(i0 & ~mx) | ((i0 + 4) & mx)];
+struct Copy16 {
+    static constexpr int P = 16 / (int)sizeof(T), J = 4 / P;
+    T v[4096];
+    __device__ __forceinline__ void put(int i, const T (&s)[4]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const T l = e > 0 ? c[e - 1] : lft;
-        const T r = e < 3 ? c[e + 1] : rgt;
-        T s = l + r;
-        s += ym[e] + yp[e];
-        s += zm[e] + zp[e];
-        Mx[e] = (s - T(6) * c[e]) * ih2;
-    }
-}
-
-constexpr int kTailElems = 3 * (4096 + 512 + 64);  // x0, x1, b of 16^3, 8^3, 4^3
-
-// LDS layout: level l's x0, x1, b follow those of levels 0..l-1.
-template <typename T>
-struct Fields {
-    T* base;
-    const TailArgs<T>* A;
-    __device__ __forceinline__ T* lev(int l) const {
-        int off = 0;
-        for (int k = 0; k < l; ++k) off += 3 * A->n[k] * A->n[k] * A->n[k];
-        return base + off;
-    }
-    __device__ __forceinline__ T* x(int l, int k) const {
-        const int N = A->n[l] * A->n[l] * A->n[l];
-        return lev(l) + k * N;
-    }
-    __device__ __forceinline__ T* b(int l) const { return x(l, 2); }
-};
-
-// One smoothing pass on tail level l of N^3 points (same buffer rotation as
-// the multi-kernel path).
-template <typename T, int N>
-__device__ int smooth_pass(const TailArgs<T>& A, const Fields<T>& F, int l, int cur, bool from_zero) {
-    constexpr int P = Geo<N>::P;
-    const T ih2 = (T)A.ih2[l];
-    const T dinv = T(1) / (T(-6) * ih2);
-    const T* b = F.b(l);
-    int prev = -1;
-    for (int k = 0; k < A.sched.steps; ++k) {
-        const T a = (T)A.sched.a[l][k], c = (T)A.sched.c[l][k];
-        if (k == 0 && from_zero) {
-            phase<T, P>([&](int i) { return c * dinv * b[i]; }, F.x(l, 0));
-            cur = 0;
-            prev = -1;
-        } else {
-            const bool use_prev = A.sched.cheb && prev >= 0;
-            const int o = use_prev ? prev : 1 - cur;
-            const T* xc = F.x(l, cur);
-            const T* xp = use_prev ? F.x(l, prev) : nullptr;
-            if constexpr (N == 16 && P == 4 * kTailThreads) {
-                const int i0 = 4 * threadIdx.x;
-                T xi[4], Mx[4], bb[4], pv[4] = {T(0), T(0), T(0), T(0)}, v[4];
-                Mx16_seg<T>(xc, i0, ih2, xi, Mx);
-                seg4<T>(bb, b + i0);
-                if (use_prev) seg4<T>(pv, xp + i0);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = xi[e] + a * (xi[e] - pv[e]) + c * dinv * (bb[e] - Mx[e]);
-                put4<T>(F.x(l, o) + i0, v);
-                __syncthreads();
-            } else {
-                phase<T, P>([&](int i) {
-                    const T Mx = Mx_at<T, N>(xc, i, ih2);
-                    const T xi = xc[i];
-                    const T pv = use_prev ? xp[i] : T(0);
-                    return xi + a * (xi - pv) + c * dinv * (b[i] - Mx);
-                }, F.x(l, o));
-            }
-            prev = cur;
-            cur = o;
+        for (int j = 0; j < J; ++j) {
+            v4i t;
+            __builtin_memcpy(&t, &s[j * P], 16);
+            *reinterpret_cast<v4i*>(v + (j * 1024 + i) * P) = t;
         }
     }
-    return cur;
+    __device__ __forceinline__ void get(T (&s)[4], int i) const {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const v4i t = *reinterpret_cast<const v4i*>(v + (j * 1024 + i) * P);
+            __builtin_memcpy(&s[j * P], &t, 16);
+        }
+    }
+};
+
+template <typename T>
+struct Shared {
+    __align__(16) Copy16<T> f[2];  // 16^3 iterate or, weighted in x, its residual
+    __align__(16) T g[2][512];     // 8^3 iterate or residual
+    T h[2][64];                    // 4^3 right-hand side and solution
+    double sA[512], sB[512], q[64], lam[8];
+};
+
+// the thread's share of a level: the 16^3 level
+template <typename T>
+struct Seg {
+    static constexpr int K = 4;
+    T x[4], b[4];
+};
+
+// M x on the segment from the published copy
+template <typename T>
+__device__ __forceinline__ void M16(const Copy16<T>& f, const T (&x)[4], T ih2, T (&Mx)[4]) {
+    const int i = threadIdx.x, r = i & ~63;  // a wave holds a plane, a quad a row
+    T ym[4], yp[4], zm[4], zp[4];
+    f.get(ym, r | ((i - 4) & 63));
+    f.get(yp, r | ((i + 4) & 63));
+    f.get(zm, (i - 64) & 1023);
+    f.get(zp, (i + 64) & 1023);
+    const T lft = quad_rot<-1>(x[3]), rgt = quad_rot<1>(x[0]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        T s = (e > 0 ? x[e - 1] : lft) + (e < 3 ? x[e + 1] : rgt);
+        s += ym[e] + yp[e];
+        s += zm[e] + zp[e];
+        Mx[e] = (s - T(6) * x[e]) * ih2;
+    }
+}
+template <typename T>
+__device__ __forceinline__ T M8(const T* g, T x, T ih2) {
+    const int i = threadIdx.x;
+    T s = g[(i & ~7) | ((i - 1) & 7)] + g[(i & ~7) | ((i + 1) & 7)];
+    s += g[(i & ~56) | ((i - 8) & 56)] + g[(i & ~56) | ((i + 8) & 56)];
+    s += g[(i - 64) & 511] + g[(i + 64) & 511];
+    return (s - T(6) * x) * ih2;
 }
 
-// Down leg on level l (N^3 points): smoothing from zero, residual into the
-// free buffer, full weighting into the coarse right-hand side.  Returns the
-// buffer holding the smoothed iterate.
-template <typename T, int N>
-__device__ int down_level(const TailArgs<T>& A, const Fields<T>& F, int l) {
-    using G = Geo<N>;
-    using Gc = Geo<N / 2>;
-    const T ih2 = (T)A.ih2[l];
-    const int cl = smooth_pass<T, N>(A, F, l, 0, true);
-    T* r = F.x(l, 1 - cl);
-    const T* xc = F.x(l, cl);
-    const T* b = F.b(l);
-    if constexpr (N == 16 && G::P == 4 * kTailThreads) {
-        const int i0 = 4 * threadIdx.x;
-        T xi[4], Mx[4], bb[4], v[4];
-        Mx16_seg<T>(xc, i0, ih2, xi, Mx);
-        seg4<T>(bb, b + i0);
+// A smoothing pass on the thread's segment of the 16^3 level (tail level l);
+// w: the copy the next publication goes to.
+template <typename T>
+__device__ __forceinline__ void smooth16(const TailArgs<T>& A, Shared<T>& S, int l, Seg<T>& u, int& w, bool from_zero) {
+    const T ih2 = (T)A.ih2[l], dinv = T(1) / (T(-6) * ih2);
+    T p[4] = {T(0), T(0), T(0), T(0)};
+    int k = 0;
+    if (from_zero) {
+        const T c = (T)A.sched.c[l][0];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = bb[e] - Mx[e];
-        put4<T>(r + i0, v);
-        __syncthreads();
-    } else {
-        phase<T, G::P>([&](int i) { return b[i] - Mx_at<T, N>(xc, i, ih2); }, r);
+        for (int e = 0; e < 4; ++e) u.x[e] = c * dinv * u.b[e];
+        k = 1;
     }
-    phase<T, Gc::P>([&](int i) {
-        int X, Y, Z;
-        Gc::coords(i, X, Y, Z);
-        T acc = T(0);
+    for (; k < A.sched.steps; ++k) {
+        const T a = (T)A.sched.a[l][k], c = (T)A.sched.c[l][k];
+        S.f[w].put(threadIdx.x, u.x);
+        __syncthreads();
+        T Mx[4];
+        M16<T>(S.f[w], u.x, ih2, Mx);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const T x = u.x[e];
+            u.x[e] = x + a * (x - p[e]) + c * dinv * (u.b[e] - Mx[e]);
+            if (A.sched.cheb) p[e] = x;
+        }
+        w ^= 1;
+    }
+}
+// The same on the thread's point of the 8^3 level (threads 0 .. 511; the
+// others pass the barriers only).
+template <typename T>
+__device__ __forceinline__ void smooth8(const TailArgs<T>& A, Shared<T>& S, int l, T& x, T b, int& w, bool from_zero) {
+    const bool on = threadIdx.x < 512;
+    const T ih2 = (T)A.ih2[l], dinv = T(1) / (T(-6) * ih2);
+    T p = T(0);
+    int k = 0;
+    if (from_zero) {
+        x = (T)A.sched.c[l][0] * dinv * b;
+        k = 1;
+    }
+    for (; k < A.sched.steps; ++k) {
+        const T a = (T)A.sched.a[l][k], c = (T)A.sched.c[l][k];
+        if (on) S.g[w][threadIdx.x] = x;
+        __syncthreads();
+        if (on) {
+            const T y = x;
+            x = y + a * (y - p) + c * dinv * (b - M8<T>(S.g[w], y, ih2));
+            if (A.sched.cheb) p = y;
+        }
+        w ^= 1;
+    }
+}
+
+// residual on 16^3, full weighting: returns b of the thread's 8^3 point
+template <typename T>
+__device__ __forceinline__ T restrict16(const TailArgs<T>& A, Shared<T>& S, int l, const Seg<T>& u, int& w) {
+    const int i = threadIdx.x;
+    T Mx[4], r[4];
+    S.f[w].put(i, u.x);
+    __syncthreads();
+    M16<T>(S.f[w], u.x, (T)A.ih2[l], Mx);
+    w ^= 1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = u.b[e] - Mx[e];
+    const T lft = quad_rot<-1>(r[3]);
+    T* v = S.f[w].v;  // [z][y][X], weighted in x
+    v[2 * i] = T(0.25) * lft + T(0.5) * r[0] + T(0.25) * r[1];
+    v[2 * i + 1] = T(0.25) * r[1] + T(0.5) * r[2] + T(0.25) * r[3];
+    __syncthreads();
+    w ^= 1;
+    T acc = T(0);
+    if (i < 512) {
+        const int X = i & 7, y0 = 2 * ((i >> 3) & 7), z0 = 2 * (i >> 6);
+#pragma unroll
         for (int dz = -1; dz <= 1; ++dz) {
             T ay = T(0);
+#pragma unroll
+            for (int dy = -1; dy <= 1; ++dy)
+                ay += (dy == 0 ? T(0.5) : T(0.25)) * v[(((z0 + dz) & 15) * 16 + ((y0 + dy) & 15)) * 8 + X];
+            acc += (dz == 0 ? T(0.5) : T(0.25)) * ay;
+        }
+    }
+    return acc;
+}
+// residual on 8^3, full weighting into S.h[0][i] by thread i < 64
+template <typename T>
+__device__ __forceinline__ void restrict8(const TailArgs<T>& A, Shared<T>& S, int l, T x, T b, int& w) {
+    const int i = threadIdx.x;
+    if (i < 512) S.g[w][i] = x;
+    __syncthreads();
+    const T r = i < 512 ? b - M8<T>(S.g[w], x, (T)A.ih2[l]) : T(0);
+    w ^= 1;
+    if (i < 512) S.g[w][i] = r;
+    __syncthreads();
+    if (i < 64) {
+        const T* g = S.g[w];
+        const int x0 = 2 * (i & 3), y0 = 2 * ((i >> 2) & 3), z0 = 2 * (i >> 4);
+        T acc = T(0);
+#pragma unroll
+        for (int dz = -1; dz <= 1; ++dz) {
+            T ay = T(0);
+#pragma unroll
             for (int dy = -1; dy <= 1; ++dy) {
-                const int fy = 2 * Y + dy, fz = 2 * Z + dz;
-                const T ax = T(0.25) * r[G::at(2 * X - 1, fy, fz)] + T(0.5) * r[G::at(2 * X, fy, fz)] +
-                             T(0.25) * r[G::at(2 * X + 1, fy, fz)];
+                const T* row = g + (((z0 + dz) & 7) * 8 + ((y0 + dy) & 7)) * 8;
+                const T ax = T(0.25) * row[(x0 - 1) & 7] + T(0.5) * row[x0] + T(0.25) * row[x0 + 1];
                 ay += (dy == 0 ? T(0.5) : T(0.25)) * ax;
             }
             acc += (dz == 0 ? T(0.5) : T(0.25)) * ay;
         }
-        return acc;
-    }, F.b(l + 1));
-    return cl;
+        S.h[0][i] = acc;
+    }
+    w ^= 1;
 }
 
-// Up leg on level l (N^3 points): x += P e, then post-smoothing.  Returns the
-// buffer holding the result.
-template <typename T, int N>
-__device__ int up_level(const TailArgs<T>& A, const Fields<T>& F, int l, int cl, const T* e) {
-    using G = Geo<N>;
-    using Gc = Geo<N / 2>;
-    T* xv = F.x(l, cl);
-    phase<T, G::P>([&](int i) {
-        int x, y, z;
-        G::coords(i, x, y, z);
-        const int X = x >> 1, Y = y >> 1, Z = z >> 1, ox = x & 1, oy = y & 1, oz = z & 1;
-        const T w = (ox ? T(0.5) : T(1)) * (oy ? T(0.5) : T(1)) * (oz ? T(0.5) : T(1));
-        T v = T(0);
-        for (int kz = 0; kz <= oz; ++kz)
-            for (int ky = 0; ky <= oy; ++ky)
-                for (int kx = 0; kx <= ox; ++kx) v += w * e[Gc::at(X + kx, Y + ky, Z + kz)];
-        return xv[i] + v;
-    }, xv);
-    return smooth_pass<T, N>(A, F, l, cl, false);
+// (a + b) / 2 where odd, else a
+template <typename T>
+__device__ __forceinline__ T mid(bool odd, T a, T b) {
+    return odd ? T(0.5) * (a + b) : a;
+}
+// P e at the thread's 8^3 point, e of 4^3 points
+template <typename T>
+__device__ __forceinline__ T prolong8(const T* e) {
+    const int i = threadIdx.x, x = i & 7, y = (i >> 3) & 7, z = (i >> 6) & 7;
+    const bool ox = x & 1, oy = y & 1, oz = z & 1;
+    const int X = x >> 1, Y = y >> 1, Z = z >> 1;
+    const int X1 = (X + ox) & 3, Y1 = (Y + oy) & 3, Z1 = (Z + oz) & 3;
+    auto row = [&](int yy, int zz) { return mid<T>(ox, e[zz * 16 + yy * 4 + X], e[zz * 16 + yy * 4 + X1]); };
+    return mid<T>(oz, mid<T>(oy, row(Y, Z), row(Y1, Z)), mid<T>(oy, row(Y, Z1), row(Y1, Z1)));
+}
+// x += P e on the thread's 16^3 segment, e of 8^3 points
+template <typename T>
+__device__ __forceinline__ void prolong16(T (&x)[4], const T* e) {
+    const int i = threadIdx.x, X = 2 * (i & 3), y = (i >> 2) & 15, z = i >> 6;
+    const bool oy = y & 1, oz = z & 1;
+    const int Y = y >> 1, Z = z >> 1, Y1 = (Y + oy) & 7, Z1 = (Z + oz) & 7;
+    T a[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        auto at = [&](int yy, int zz) { return e[zz * 64 + yy * 8 + X + j]; };
+        a[j] = mid<T>(oz, mid<T>(oy, at(Y, Z), at(Y1, Z)), mid<T>(oy, at(Y, Z1), at(Y1, Z1)));
+    }
+    const T a2 = quad_rot<1>(a[0]);
+    x[0] += a[0];
+    x[1] += T(0.5) * (a[0] + a[1]);
+    x[2] += a[1];
+    x[3] += T(0.5) * (a[1] + a2);
 }
 
 // Exact zero-mean solve on the coarsest level (NC^3 points) in double with the
@@ -314,54 +328,58 @@ __device__ void coarsest4(const T* bl, T* xl, const double* q, const double* lam
     __syncthreads();
 }
 
-template <typename T>
+// HAS16: the first tail level has 16^3 points (else 8^3); CST: points per side
+// of the coarsest level.
+template <typename T, bool HAS16, int CST>
 __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<T> A) {
-    __shared__ __align__(16) T fields[kTailElems];
-    __shared__ double sA[512];
-    __shared__ double sB[512];
-    __shared__ double q[64];
-    __shared__ double lam[8];
+    __shared__ Shared<T> S;
+    static_assert(sizeof(S.f) >= kSumLanes * sizeof(double), "the sums fit the tail's LDS");
     if (blockIdx.x == 1) {  // the outer sums, beside the tail
-        finish_sums(A.sums, reinterpret_cast<double*>(fields));
+        finish_sums(A.sums, reinterpret_cast<double*>(&S));
         return;
     }
-    const Fields<T> F{fields, &A};
-    unsigned curbits = 0;  // bit l: buffer holding level l's iterate (no private array)
-    const int nl = A.nlev;
-    const int tid = threadIdx.x;
-    const int ncst = A.n[nl - 1];
-    {   // right-hand side of the first tail level and the coarsest basis from
-        // global memory, all loads in flight together
-        const int N0 = A.n[0] * A.n[0] * A.n[0];
-        T* b0 = F.b(0);
-        for (int i = tid; i < N0; i += kTailThreads) b0[i] = A.b[0][i];
-        if (tid < ncst * ncst) q[tid] = A.Q[tid];
-        if (tid < ncst) lam[tid] = A.lam1[tid];
+    constexpr bool HAS8 = CST == 4;
+    constexpr int l8 = HAS16 ? 1 : 0;
+    static_assert(HAS16 || HAS8, "at least one level above the coarsest");
+    const int i = threadIdx.x;
+    Seg<T> u;
+    T x8 = T(0), b8 = T(0);
+    int w16 = 0, w8 = 0;
+    if constexpr (HAS16) {
+        ldrow<T, 4>(u.b, A.b[0] + 4 * i);
+    } else {
+        if (i < 512) b8 = A.b[0][i];
+    }
+    if (i < CST * CST) S.q[i] = A.Q[i];
+    if (i < CST) S.lam[i] = A.lam1[i];
+    if constexpr (HAS16) {
+        smooth16<T>(A, S, 0, u, w16, true);
+        b8 = restrict16<T>(A, S, 0, u, w16);
+    }
+    T* e8 = S.g[0];  // solution of the 8^3 level
+    if constexpr (HAS8) {
+        smooth8<T>(A, S, l8, x8, b8, w8, true);
+        restrict8<T>(A, S, l8, x8, b8, w8);  // lane i of the first wave wrote what it reads next
+        coarsest4<T>(S.h[0], S.h[1], S.q, S.lam);
+        if (i < 512) x8 += prolong8<T>(S.h[1]);
+        smooth8<T>(A, S, l8, x8, b8, w8, false);
+        if constexpr (HAS16) {
+            // the copy the last step did not read
+            e8 = S.g[w8];
+            if (i < 512) e8[i] = x8;
+            __syncthreads();
+        } else {
+            if (i < 512) A.x0[0][i] = x8;
+        }
+    } else {
+        if (i < 512) S.g[1][i] = b8;
         __syncthreads();
+        coarsest<T, 8>(S.g[1], e8, S.sA, S.sB, S.q, S.lam);
     }
-    // ---------------- down leg
-    for (int l = 0; l + 1 < nl; ++l) {
-        const int cl = A.n[l] == 16 ? down_level<T, 16>(A, F, l) : down_level<T, 8>(A, F, l);
-        curbits = (curbits & ~(1u << l)) | ((unsigned)cl << l);
-    }
-    // ---------------- coarsest: exact zero-mean solve in double (separable basis)
-    {
-        const int l = nl - 1;
-        if (ncst == 8) coarsest<T, 8>(F.b(l), F.x(l, 0), sA, sB, q, lam);
-        else coarsest4<T>(F.b(l), F.x(l, 0), q, lam);
-        curbits &= ~(1u << l);
-    }
-    // ---------------- up leg
-    for (int l = nl - 2; l >= 0; --l) {
-        const T* e = F.x(l + 1, (curbits >> (l + 1)) & 1);
-        const int cl = (curbits >> l) & 1;
-        const int cn = A.n[l] == 16 ? up_level<T, 16>(A, F, l, cl, e) : up_level<T, 8>(A, F, l, cl, e);
-        curbits = (curbits & ~(1u << l)) | ((unsigned)cn << l);
-    }
-    {   // result of the first tail level to global memory (always its buffer x0)
-        const int N0 = A.n[0] * A.n[0] * A.n[0];
-        const T* x0 = F.x(0, curbits & 1);
-        for (int i = tid; i < N0; i += kTailThreads) A.x0[0][i] = x0[i];
+    if constexpr (HAS16) {
+        prolong16<T>(u.x, e8);
+        smooth16<T>(A, S, 0, u, w16, false);
+        strow<T, 4>(A.x0[0] + 4 * i, u.x);
     }
 }
 
@@ -377,11 +395,10 @@ hipError_t launch_tail(const TailArgs<T>& args, hipStream_t s) {
         if (coarsest ? (nl != 8 && nl != 4) : (nl != 16 && nl != 8)) return hipErrorInvalidValue;
         if (l > 0 && nl * 2 != args.n[l - 1]) return hipErrorInvalidValue;
     }
-    int elems = 0;
-    for (int l = 0; l < args.nlev; ++l) elems += 3 * args.n[l] * args.n[l] * args.n[l];
-    if (elems > kTailElems) return hipErrorInvalidValue;
-    static_assert(sizeof(T) * kTailElems >= kSumLanes * sizeof(double), "the sums fit the tail's LDS");
-    hipLaunchKernelGGL((k_tail<T>), dim3(args.sums.count > 0 ? 2 : 1), dim3(kTailThreads), 0, s, args);
+    const dim3 grid(args.sums.count > 0 ? 2 : 1), block(kTailThreads);
+    if (args.n[0] == 8) hipLaunchKernelGGL((k_tail<T, false, 4>), grid, block, 0, s, args);
+    else if (args.n[args.nlev - 1] == 8) hipLaunchKernelGGL((k_tail<T, true, 8>), grid, block, 0, s, args);
+    else hipLaunchKernelGGL((k_tail<T, true, 4>), grid, block, 0, s, args);
     return hipGetLastError();
 }
 

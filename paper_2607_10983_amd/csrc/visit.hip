@@ -401,7 +401,7 @@ __global__ __launch_bounds__(kP) void k_visit64_post(const float* __restrict__ x
 }  // namespace
 
 // 32^3 in both types, 64^3 in float (tiles of 8 x 8 x 4 points took 7.1 + 9.5
-// us there, 64 x 8 rows @64@; in double, degree 4, two tiles per CU took longer
+// us there, 64 x 8 rows 5.2 + 6.5; in double, degree 4, two tiles per CU took longer
 // than the six launches they replace: 20 us more per cycle).
 bool visit_pre_applies(int n, int degree, size_t elem) {
     return degree >= 1 &&
