@@ -680,6 +680,8 @@ hipError_t launch_residual_restrict(const OpDesc<TC>& op, const T* x, const T* b
                                     hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, const FirstStep<T>& first) {
     if (op.coeff == nullptr && x != nullptr && row_kernels_apply(op.n))
         return launch_rr_row<T>(op.n, op.ih2, x, b, coarse, s, ev0, ev1);
+    if (op.coeff != nullptr && x != nullptr && var_rr_applies(op.n, sizeof(T)))
+        return launch_var_rr<T, TC>(op.n, op.ih2, op.coeff, x, b, coarse, first.C, first.x1, first.c0, s, ev0, ev1);
     if (scratch != nullptr && x != nullptr) {
         if (op.coeff != nullptr && var_row_kernels_apply(op.n)) {
             hipError_t e = launch_var_resid_row<T, TC>(op.n, op.ih2, op.coeff, x, b, scratch, s, ev0, ev1);

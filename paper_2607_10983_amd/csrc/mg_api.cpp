@@ -620,10 +620,12 @@ mg_status residual_restrict_level(mg_ctx* c, int l, bool cycle = false) {
     }
     HIPCHK(c, launch_residual_restrict<T, T>(op_of<T>(L), (const T*)L.x[L.cur], (const T*)L.b, (T*)Lc.b,
                                              (T*)L.x[other(L.cur)], c->stream, ev0, ev1, first));
-    // seven-point: x, b read, r_{l+1} written; 19-point: the timed pass forms
-    // the fine residual (x, b, C read, r written) and a second pass restricts it
+    // x, b [, C] read, r_{l+1} written; 19-point rows without the fused pass: the timed
+    // one forms the fine residual (x, b, C read, r written) and a second one restricts it
     const double N = (double)L.N, s = sizeof(T);
-    const double bytes = c->var ? N * (3.0 * s + 6.0 * s) : N * (2.0 + 1.0 / 8.0) * s;
+    const double bytes = !c->var                         ? N * (2.0 + 1.0 / 8.0) * s
+                         : var_rr_applies(L.n, sizeof(T)) ? N * (2.0 + 6.0 + 1.0 / 8.0) * s
+                                                          : N * (3.0 + 6.0) * s;
     return time_end(c, fine, MG_TIME_TRANSFER, bytes);
 }
 

@@ -31,6 +31,13 @@ hipError_t launch_var_smooth_pair(int n, double ih2, const TC* C, const T* x, co
 template <typename T, typename TC>
 hipError_t launch_var_resid_row(int n, double ih2, const TC* C, const T* x, const T* b, T* out, hipStream_t s,
                                 hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// coarse = R (b - M x) ((n/2)^3 points); with cx1 also the coarse level's first
+// step from zero, cx1 = cc0 D^-1 coarse with D of the coarse coefficients cC.
+// Levels for which var_rr_applies; hipErrorInvalidValue otherwise.
+bool var_rr_applies(int n, size_t elem);
+template <typename T, typename TC>
+hipError_t launch_var_rr(int n, double ih2, const TC* C, const T* x, const T* b, T* coarse, const T* cC, T* cx1,
+                         double cc0, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 template <typename TA, typename TR, typename TE, typename TC>
 hipError_t launch_var_outer_row(int n, double ih2, const TC* C, const double* phi_in, const TE* e, double* phi_out,
                                 const double* b, Mean bmean, TR* r, TR* x1, double c0, double* partials,

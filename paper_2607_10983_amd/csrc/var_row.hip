@@ -18,8 +18,10 @@
 // D = -sum_a (f_a+ + f_a-) / h^2 its diagonal.
 #include "var_row.h"
 
+#include "fma.h"
 #include "launch.h"
 #include "row.h"
+#include "stencil.h"
 
 namespace mg {
 namespace {
@@ -669,6 +671,113 @@ __global__ __launch_bounds__(64 * W) void k_var_resid_lds(int n, T ih2, const TC
 }
 
 // =====================================================================================
+// residual and full weighting in one pass: coarse = R (b - M x)
+// =====================================================================================
+// The residual rows never leave the block: kRrWaves = 9 waves form rows
+// 2Y - 1 .. 2Y + 7 of a plane (one row of nine belongs to the neighbour too),
+// weight them in x and publish the half rows, and the four waves on even rows
+// weight those in y one plane later and add them up along z.  One barrier per
+// plane, as in the residual kernel.  cx1 (may be null): the coarse level's
+// first smoothing step from zero, cc0 coarse / D, cC its coefficients.
+// Rounding of the weights as in k_restrict (x, y, z, each left to right).
+constexpr int kRrWaves = 9;
+template <typename T, typename TC, int VEC, bool ZQ>
+__global__ __launch_bounds__(64 * kRrWaves) void k_var_rr_lds(int n, T ih2, const TC* __restrict__ C,
+                                                              const T* __restrict__ x, const T* __restrict__ b,
+                                                              T* __restrict__ coarse, const T* __restrict__ cC,
+                                                              T* __restrict__ cx1, T cc0, T cih2, int nz, int nyb) {
+    constexpr int W = kRrWaves, NR = 64 * VEC, M = NR / 2, CV = VEC > 1 ? VEC / 2 : 1;
+    constexpr size_t N = (size_t)NR * NR * NR, Nc = N / 8;
+    __shared__ T ring[4][W + 2][NR];
+    __shared__ T half[2][W][M];  // residual rows weighted in x, by plane parity
+    const RowGrid g{NR, NR - 1}, gc{M, M - 1};
+    const int lb = xcd_logical(blockIdx.x, gridDim.x);
+    const int yb = lb % nyb, zc = lb / nyb;
+    const int w = wave_id();
+    const int y0 = yb * (W - 1) - 1, y = y0 + w;  // row -1 wraps for loads
+    const int z0 = zc * nz - 1;                   // first residual plane
+    const int lane = threadIdx.x & 63;
+    const size_t off = (size_t)lane * VEC;
+    const bool lo = w == 0, hi = w == W - 1;
+    const int yh = lo ? y0 - 1 : y0 + W;
+    const Ring<T, VEC, W> rg{ring, w, lo ? 0 : W + 1, lane, lo || hi};
+    const PlainRows<T, T, VEC> src{x};
+    T U[3][3][VEC], hr[VEC], xn[VEC], hn[VEC];
+    ring_start<T, VEC, W>(rg, U, hr, src, g, y, yh, z0, off);
+    CQueue<T, VEC> q;
+    cq_load<ZQ, T, TC, VEC>(q, 0, C, N, g, y, z0 - 1, off);
+    cq_load<ZQ, T, TC, VEC>(q, 1, C, N, g, y, z0, off);
+    const bool even = (w & 1) != 0;                            // the wave's row is a coarse row
+    const bool has = VEC > 1 || (lane & 1) == 0;               // the lane holds coarse points
+    const size_t coff = VEC > 1 ? (size_t)lane * CV : lane >> 1;
+    T acc[CV] = {};
+    // plane k (z0 + k) of the half rows into the coarse rows
+    auto collect = [&](int k) {
+#pragma clang fp contract(off)
+        T m[CV], c[CV], p[CV], a[CV];
+        ldrow<T, CV>(m, half[k & 1][w - 1] + coff);
+        ldrow<T, CV>(c, half[k & 1][w] + coff);
+        ldrow<T, CV>(p, half[k & 1][w + 1] + coff);
+#pragma unroll
+        for (int e = 0; e < CV; ++e) a[e] = fw3<T>(m[e], c[e], p[e]);
+        if (k & 1) {
+#pragma unroll
+            for (int e = 0; e < CV; ++e) acc[e] = acc[e] + T(0.5) * a[e];
+            return;
+        }
+        if (k > 0) {
+            const int Y = y >> 1, Z = (z0 + k - 1) >> 1;
+            T o[CV];
+#pragma unroll
+            for (int e = 0; e < CV; ++e) o[e] = acc[e] + T(0.25) * a[e];
+            const size_t r = gc.row(Y, Z) + coff;
+            if (has) strow<T, CV>(coarse + r, o);
+            if (cx1) {
+                T D[CV];
+                if constexpr (VEC > 1) var19_diag<T, T, CV>(cC, Nc, gc, Y, Z, coff, cih2, D);
+                else D[0] = var_diag<T, T>(cC, Nc, Grid{M, M - 1}, lane >> 1, Y, Z, cih2);
+#pragma unroll
+                for (int e = 0; e < CV; ++e) o[e] = cc0 * o[e] / D[e];
+                if (has) strow<T, CV>(cx1 + r, o);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < CV; ++e) acc[e] = T(0.25) * a[e];
+    };
+    for (int k = 0; k <= nz; ++k) {
+        const int z = z0 + k;
+        const bool more = k < nz;
+        if (more) {
+            src.load(xn, g.row(y, z + 2) + off);
+            if (rg.edge) src.load(hn, g.row(yh, z + 2) + off);
+        }
+        ring_publish<T, VEC, W>(rg, U, hr, z);
+        cq_load<ZQ, T, TC, VEC>(q, 2, C, N, g, y, z + 1, off);
+        constexpr bool EARLY = kVarCrowsEarly && sizeof(T) == sizeof(float);  // as in k_var_resid_lds
+        CRows<T, VEC> cr;
+        if constexpr (EARLY) cr_load<T, TC, VEC>(cr, C, N, g, y, z, off);
+        T bb[VEC], Mu[VEC], D[VEC], r[VEC];
+        ldrow<T, VEC>(bb, b + g.row(y, z) + off);
+        __syncthreads();
+        if (even && k > 0) collect(k - 1);
+        ring_gather<T, VEC, W>(rg, U, z);
+        if constexpr (!EARLY) cr_load<T, TC, VEC>(cr, C, N, g, y, z, off);
+        var19_row_c<ZQ, T, TC, VEC>(U, q, cr, C, N, g, y, z, off, ih2, Mu, D);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) r[e] = bb[e] - Mu[e];
+        T rp[VEC], rm[VEC], h[CV];
+        shifts<T, VEC>(r, rp, rm);
+#pragma unroll
+        for (int e = 0; e < CV; ++e) h[e] = fw3<T>(rm[2 * e], r[2 * e], rp[2 * e]);
+        if (has) strow<T, CV>(half[k & 1][w] + coff, h);
+        if (more) ring_shift<T, VEC, W>(rg, U, hr, xn, hn);
+        cq_shift<ZQ, T, VEC>(q);
+    }
+    __syncthreads();
+    if (even) collect(nz);
+}
+
+// =====================================================================================
 // outer defect correction in TA: value = phi (+ e), r = (b - bmean) - M value,
 // optional x1 = c0 D^-1 r, partial sums of r^2
 // =====================================================================================
@@ -913,6 +1022,33 @@ hipError_t launch_var_resid_row(int n, double ih2, const TC* C, const T* x, cons
     return hipGetLastError();
 }
 
+// Residual and restriction in one pass on rows of up to 1 KB, chunks of at
+// most kRrNz planes giving at least 256 blocks.  Against the residual kernel
+// and a restriction launch: float 256^3 169 -> 125 us (chunks of 16 planes
+// 128, of 8 planes 136), 128^3 21.7 -> 18.0, 64^3 9.6 -> 5.6; double 128^3
+// 37.6 -> 28.5, 64^3 11.4 -> 7.3.  Rows of 2 KB, where one block fits a CU's
+// LDS, were slower fused: a cycle of 256^3 double 2.55 -> 2.63 ms, of 512^3
+// mixed 12.8 -> 13.2.
+constexpr int kRrNz = 32;
+bool var_rr_applies(int n, size_t elem) { return var_row_kernels_apply(n) && (size_t)n * elem <= 1024; }
+
+template <typename T, typename TC>
+hipError_t launch_var_rr(int n, double ih2, const TC* C, const T* x, const T* b, T* coarse, const T* cC, T* cx1,
+                         double cc0, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    if (!var_rr_applies(n, sizeof(T)) || b == nullptr) return hipErrorInvalidValue;
+    const int nyb = n / (kRrWaves - 1);
+    int nz = kRrNz;
+    while (nz > 2 && nyb * (n / nz) < 256) nz >>= 1;
+    DISPATCH_VEC(n, {
+        if constexpr (64 * VEC * sizeof(T) <= 1024)
+            MG_LAUNCH((k_var_rr_lds<T, TC, VEC, (VEC <= 4)>), dim3(nyb * (n / nz)), dim3(64 * kRrWaves), s, ev0, ev1,
+                      n, (T)ih2, C, x, b, coarse, cC, cx1, (T)cc0, (T)(ih2 / 4.0), nz, nyb);
+        else
+            return hipErrorInvalidValue;
+    })
+    return hipGetLastError();
+}
+
 template <typename TA, typename TR, typename TE, typename TC>
 hipError_t launch_var_outer_row(int n, double ih2, const TC* C, const double* phi_in, const TE* e, double* phi_out,
                                 const double* b, Mean bmean, TR* r, TR* x1, double c0, double* partials,
@@ -937,7 +1073,9 @@ hipError_t launch_var_outer_row(int n, double ih2, const TC* C, const double* ph
                                                       double, double, double, double, hipStream_t, hipEvent_t,     \
                                                       hipEvent_t);                                                 \
     template hipError_t launch_var_resid_row<T, TC>(int, double, const TC*, const T*, const T*, T*, hipStream_t,   \
-                                                    hipEvent_t, hipEvent_t);
+                                                    hipEvent_t, hipEvent_t);                                       \
+    template hipError_t launch_var_rr<T, TC>(int, double, const TC*, const T*, const T*, T*, const T*, T*, double, \
+                                             hipStream_t, hipEvent_t, hipEvent_t);
 INST_VAR(float, float)
 INST_VAR(double, double)
 INST_VAR(double, float)
