@@ -2,29 +2,29 @@
 //
 // A visit of that level with v smoothing steps took 2 v + 3 launches, each of
 // them bound by its launch (about 4 us) and by one trip to L2, not by its
-// work.  Here it takes two.  A workgroup owns a tile of 8 x 8 x 4 fine points
+// work.  Here it takes two.  A workgroup owns a tile of 8 x 4 x 4 fine points
 // and keeps the tile with a halo as wide as the visit needs in LDS: two copies
 // of the iterate and the six coefficient fields.  Every application of the
 // operator shrinks the valid region by one point per side, so neighbouring
 // tiles compute their common halo twice and never wait for each other:
 //
 //   pre:  x_2 .. x_v from x_1 (written by the kernel that produced b), the
-//         residual, its full weighting; writes x_v on the tile, the 4 x 4 x 2
+//         residual, its full weighting; writes x_v on the tile, the 4 x 2 x 2
 //         coarse right-hand side and the coarse level's own first step;
 //   post: x_0 = x + P e, then v steps; writes x_v on the tile.
 //
-// The tile is small on purpose.  At 32^3 it gives 128 workgroups: the
-// redundant points (about 8 applications per point of a visit instead of 3)
-// cost less than leaving CUs idle, and the halo'd coefficients (47 to 59 KB in
-// float, twice that in double, for three steps) still fit LDS, from which one
-// application reads its 19 iterate and 21 coefficient values at constant
-// offsets.
+// The tile is small on purpose.  At 32^3 it gives one workgroup per CU: the
+// redundant points (10 to 14 applications per point of a visit instead of 3)
+// cost less than leaving CUs idle, and the halo'd coefficients still fit LDS,
+// from which one application reads its 19 iterate and 21 coefficient values at
+// constant offsets.
 //
-// Measured at 32^3, degree 3: 10.3 + 10.1 us in float and 11.2 + 11.9 us in
-// double, in place of nine launches of 38 to 41 us.  The 64^3 level keeps its
-// separate kernels: 1024 tiles are four rounds of the chip's LDS, and the
+// Measured at 32^3, degree 3: 9.0 + 7.0 us in float and 9.4 + 9.0 us in double
+// (tiles of 8 x 8 x 4 points, 128 workgroups: 10.5 + 8.3 and 11.5 + 10.5), in
+// place of nine launches of 38 to 41 us.  The 64^3 level keeps its separate
+// kernels: 1024 tiles of 8 x 8 x 4 are four rounds of the chip's LDS, and the
 // visits took 27.5 + 26.4 us in float and 45.5 + 44.0 us in double, against
-// about 37 and 55 us for the eight launches.
+// about 37 and 55 us for the launches.
 //
 // The point formula is that of var_Mu and k_smooth (stencil.h, kernels.hip).
 #include "var_visit.h"
@@ -35,7 +35,7 @@
 namespace mg {
 namespace {
 
-constexpr int kTX = 8, kTY = 8, kTZ = 4;  // tile
+constexpr int kTX = 8, kTY = 4, kTZ = 4;  // tile
 constexpr int kThrV = 512;
 
 struct VisitSteps {
