@@ -15,8 +15,10 @@
 //   - the tangential coefficients around a segment are loaded once: into
 //     registers in float (40 of the 128 a thread of a 1024-thread block may
 //     use), into LDS in double (96 KB), where they do not fit.
-// Measured (16^3, 8^3, dense 4^3, degree 3; one launch): 18.9 us in float,
-// 28.2 us in double, in place of 19 launches of 74 us.  Reading the x
+// Measured (16^3, 8^3, dense 4^3, degree 3; one launch): 18.6 us in float,
+// 27.5 us in double, in place of 19 launches of 74 us (19.2 and 28.5 with the
+// residual weighted from 27 reads, the prolongation point by point and the
+// coarsest operator loaded where it is applied).  Reading the x
 // neighbours as single LDS values at the segments' stride (bank conflicts)
 // took 21 and 53 us, and an earlier form that re-read the coefficients from
 // L2 in each application was as slow as the launches.  256^3 mixed solve
@@ -356,7 +358,7 @@ __device__ __forceinline__ T Mu8(const T* u, const Pos8& p, T c, const Faces8<T>
 template <typename T, int M>
 __device__ __forceinline__ T weigh(const T* f, int i) {
     constexpr int N = 2 * M;
-    auto r = [&](int j) { return f[N == 16 ? Seg<T>::at(j) : j]; };
+    auto r = [&](int j) { return f[j]; };
     const int X = i % M, Y = (i / M) % M, Z = i / (M * M);
     T acc = T(0);
 #pragma unroll
@@ -530,9 +532,31 @@ __global__ __launch_bounds__(tail_threads<T>()) void k_var_tail(VarTailArgs<T> A
 #pragma unroll
             for (int e = 0; e < 4; ++e) r[s][e] = b16[s][e] - r[s][e];
         }
-        publish16(r);
+        // weighted in x before it is published: [z][y][X], half the values and
+        // 9 reads per coarse point instead of 27
+        if constexpr (REG) buf ^= 1;
+        else __syncthreads();
+        T* h = x16(buf);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const T l = quad_rot<-1>(r[s][3]);
+            const int v = 2 * (t + s * NT);
+            h[v] = T(0.25) * l + T(0.5) * r[s][0] + T(0.25) * r[s][1];
+            h[v + 1] = T(0.25) * r[s][1] + T(0.5) * r[s][2] + T(0.25) * r[s][3];
+        }
+        __syncthreads();
         if (t < kP8) {
-            b8v = weigh<T, 8>(x16(buf), t);
+            const int X = t & 7, y0 = 2 * ((t >> 3) & 7), z0 = 2 * (t >> 6);
+            T acc = T(0);
+#pragma unroll
+            for (int dz = -1; dz <= 1; ++dz) {
+                T ay = T(0);
+#pragma unroll
+                for (int dy = -1; dy <= 1; ++dy)
+                    ay += (dy == 0 ? T(0.5) : T(0.25)) * h[(((z0 + dz) & 15) * 16 + ((y0 + dy) & 15)) * 8 + X];
+                acc += (dz == 0 ? T(0.5) : T(0.25)) * ay;
+            }
+            b8v = acc;
             if constexpr (DENSE8) S.b8[t] = b8v;
         }
     }
@@ -548,6 +572,13 @@ __global__ __launch_bounds__(tail_threads<T>()) void k_var_tail(VarTailArgs<T> A
             k8.load(C + 3 * kP8, C + 4 * kP8, C + 5 * kP8, p8);
             x8v = (T)A.sched.c[L8][0] * b8v * f8.dinv;
         }
+        // the coarsest level's operator, for the end of this leg: each wave forms
+        // NR consecutive rows, one column per lane
+        constexpr int NR = kP4 / (NT / 64);
+        const int w = t >> 6, lane = t & 63;
+        double gr[NR];
+#pragma unroll
+        for (int j = 0; j < NR; ++j) gr[j] = A.G[(NR * w + j) * kP4 + lane];
         publish8(x8v);
         for (int k = 1; k < steps; ++k) {
             step8(k, cheb && k > 1);
@@ -558,13 +589,11 @@ __global__ __launch_bounds__(tail_threads<T>()) void k_var_tail(VarTailArgs<T> A
         publish8(r8);
         if (t < kP4) S.b4[t] = weigh<T, 4>(S.x8 + buf8 * kP8, t);
         __syncthreads();
-        // coarsest: e = G b, each wave forms NR consecutive rows, one column per lane
-        constexpr int NR = kP4 / (NT / 64);
-        const int w = t >> 6, lane = t & 63;
+        // coarsest: e = G b
         const double rb = (double)S.b4[lane];
         double acc[NR];
 #pragma unroll
-        for (int j = 0; j < NR; ++j) acc[j] = A.G[(NR * w + j) * kP4 + lane] * rb;
+        for (int j = 0; j < NR; ++j) acc[j] = gr[j] * rb;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
@@ -606,9 +635,20 @@ __global__ __launch_bounds__(tail_threads<T>()) void k_var_tail(VarTailArgs<T> A
         const T* e = S.x8 + buf8 * kP8;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const int v = t + s * NT, y = (v >> 2) & 15, z = v >> 6;
+            // the segment's coarse points 2 q, 2 q + 1, and 2 q + 2 from the next lane
+            const int v = t + s * NT, X = 2 * (v & 3), y = (v >> 2) & 15, z = v >> 6;
+            const int Y = y >> 1, Z = z >> 1, Y1 = (Y + (y & 1)) & 7, Z1 = (Z + (z & 1)) & 7;
+            T a[2];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) x[s][k] += interp<T, 8>(e, (v & 3) * 4 + k, y, z);
+            for (int j = 0; j < 2; ++j) {
+                auto at = [&](int yy, int zz) { return e[zz * 64 + yy * 8 + X + j]; };
+                a[j] = T(0.5) * (T(0.5) * (at(Y, Z) + at(Y1, Z)) + T(0.5) * (at(Y, Z1) + at(Y1, Z1)));
+            }
+            const T a2 = quad_rot<1>(a[0]);
+            x[s][0] += a[0];
+            x[s][1] += T(0.5) * (a[0] + a[1]);
+            x[s][2] += a[1];
+            x[s][3] += T(0.5) * (a[1] + a2);
         }
         publish16(x);
         for (int k = 0; k < steps; ++k) {
