@@ -15,8 +15,8 @@ LIB = os.path.join(HERE, "libmg.so")
 OBJDIR = os.path.join(ROOT, "_build")
 SOURCES = [os.path.join(HERE, "csrc", f)
            for f in ("flat_row.hip", "pair_tile.hip", "var_row.hip", "kernels.hip", "tail.hip", "var_tail.hip",
-                     "var_visit.hip", "visit.hip", "setup.hip", "pcg.hip", "pcg_row.hip", "readout.hip", "noalloc.hip",
-                     "mg_api.cpp")]
+                     "var_visit.hip", "visit.hip", "setup.hip", "pcg.hip", "pcg_row.hip", "readout.hip", "geometry_bwd.hip",
+                     "noalloc.hip", "mg_api.cpp")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

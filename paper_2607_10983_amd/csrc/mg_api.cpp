@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "flat_row.h"
+#include "geometry_bwd.h"
 #include "kernels.h"
 #include "pcg_row.h"
 #include "setup.h"
@@ -1736,16 +1737,19 @@ mg_status mg_geometry_bwd(int n, double h, const double* psi, const double* Cbar
     if (!is_pow2(n) || n < 4 || n > 2048 || !(h > 0) || !psi || !Cbar || !psibar) return MG_ERR_INVALID;
     const double ih2 = 1.0 / (h * h);
     const size_t N = (size_t)n * n * n;
-    double* Jbar = nullptr;
-    if (hipMalloc((void**)&Jbar, 6 * N * sizeof(double)) != hipSuccess) {
+    hipStream_t s = (hipStream_t)stream;
+    if (!geometry_bwd_overlaps(N, psi, Cbar, sqrtgbar, psibar))
+        return launch_geometry_bwd(n, ih2, psi, Cbar, sqrtgbar, psibar, s) == hipSuccess ? MG_OK : MG_ERR_HIP;
+    // the result replaces an input that other blocks still read: through a temporary
+    double* tmp = nullptr;
+    if (hipMalloc((void**)&tmp, N * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
         return MG_ERR_NOMEM;
     }
-    hipStream_t s = (hipStream_t)stream;
-    hipError_t e = launch_geometry_bwd_cell(n, ih2, psi, Cbar, sqrtgbar, Jbar, s);
-    if (e == hipSuccess) e = launch_hessian_adjoint(n, ih2, Jbar, psibar, s);
+    hipError_t e = launch_geometry_bwd(n, ih2, psi, Cbar, sqrtgbar, tmp, s);
+    if (e == hipSuccess) e = launch_shift(N, tmp, 0.0, psibar, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFree(Jbar);
+    (void)hipFree(tmp);
     return e == hipSuccess ? MG_OK : MG_ERR_HIP;
 }
 
