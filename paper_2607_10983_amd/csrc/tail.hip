@@ -225,38 +225,58 @@ __device__ __forceinline__ void restrict8(const TailArgs<T>& A, Shared<T>& S, in
     w ^= 1;
 }
 
-// (a + b) / 2 where odd, else a
+// The interpolation weight of a fine point and the sum over its coarse points
+// in the order z, y, x, each product exact (a power of two): the terms of an
+// even coordinate's second point are zero instead of branches.
 template <typename T>
-__device__ __forceinline__ T mid(bool odd, T a, T b) {
-    return odd ? T(0.5) * (a + b) : a;
+__device__ __forceinline__ T weight(bool ox, bool oy, bool oz) {
+    return (ox ? T(0.5) : T(1)) * (oy ? T(0.5) : T(1)) * (oz ? T(0.5) : T(1));
+}
+template <typename T>
+__device__ __forceinline__ T interp(const T (&r)[4][2], bool ox, bool oy, bool oz) {
+    const T w = weight<T>(ox, oy, oz);
+    const bool on[4] = {true, oy, oz, oy && oz};
+    T v = T(0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {  // rows (Y, Z), (Y + 1, Z), (Y, Z + 1), (Y + 1, Z + 1)
+        v += on[k] ? w * r[k][0] : T(0);
+        v += on[k] && ox ? w * r[k][1] : T(0);
+    }
+    return v;
 }
 // P e at the thread's 8^3 point, e of 4^3 points
 template <typename T>
 __device__ __forceinline__ T prolong8(const T* e) {
     const int i = threadIdx.x, x = i & 7, y = (i >> 3) & 7, z = (i >> 6) & 7;
-    const bool ox = x & 1, oy = y & 1, oz = z & 1;
-    const int X = x >> 1, Y = y >> 1, Z = z >> 1;
-    const int X1 = (X + ox) & 3, Y1 = (Y + oy) & 3, Z1 = (Z + oz) & 3;
-    auto row = [&](int yy, int zz) { return mid<T>(ox, e[zz * 16 + yy * 4 + X], e[zz * 16 + yy * 4 + X1]); };
-    return mid<T>(oz, mid<T>(oy, row(Y, Z), row(Y1, Z)), mid<T>(oy, row(Y, Z1), row(Y1, Z1)));
+    const int X = x >> 1, Y = y >> 1, Z = z >> 1, X1 = (X + 1) & 3, Y1 = (Y + 1) & 3, Z1 = (Z + 1) & 3;
+    const int row[4] = {Z * 16 + Y * 4, Z * 16 + Y1 * 4, Z1 * 16 + Y * 4, Z1 * 16 + Y1 * 4};
+    T r[4][2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        r[k][0] = e[row[k] + X];
+        r[k][1] = e[row[k] + X1];
+    }
+    return interp<T>(r, x & 1, y & 1, z & 1);
 }
-// x += P e on the thread's 16^3 segment, e of 8^3 points
+// x += P e on the thread's 16^3 segment, e of 8^3 points: coarse points X, X + 1
+// of each row, X + 2 from the next lane of the quad
 template <typename T>
 __device__ __forceinline__ void prolong16(T (&x)[4], const T* e) {
     const int i = threadIdx.x, X = 2 * (i & 3), y = (i >> 2) & 15, z = i >> 6;
     const bool oy = y & 1, oz = z & 1;
-    const int Y = y >> 1, Z = z >> 1, Y1 = (Y + oy) & 7, Z1 = (Z + oz) & 7;
-    T a[2];
+    const int Y = y >> 1, Z = z >> 1, Y1 = (Y + 1) & 7, Z1 = (Z + 1) & 7;
+    const int row[4] = {Z * 64 + Y * 8, Z * 64 + Y1 * 8, Z1 * 64 + Y * 8, Z1 * 64 + Y1 * 8};
+    T lo[4][2], hi[4][2];  // (X, X + 1) and (X + 1, X + 2)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        auto at = [&](int yy, int zz) { return e[zz * 64 + yy * 8 + X + j]; };
-        a[j] = mid<T>(oz, mid<T>(oy, at(Y, Z), at(Y1, Z)), mid<T>(oy, at(Y, Z1), at(Y1, Z1)));
+    for (int k = 0; k < 4; ++k) {
+        lo[k][0] = e[row[k] + X];
+        lo[k][1] = hi[k][0] = e[row[k] + X + 1];
+        hi[k][1] = quad_rot<1>(lo[k][0]);
     }
-    const T a2 = quad_rot<1>(a[0]);
-    x[0] += a[0];
-    x[1] += T(0.5) * (a[0] + a[1]);
-    x[2] += a[1];
-    x[3] += T(0.5) * (a[1] + a2);
+    x[0] = x[0] + interp<T>(lo, false, oy, oz);
+    x[1] = x[1] + interp<T>(lo, true, oy, oz);
+    x[2] = x[2] + interp<T>(hi, false, oy, oz);
+    x[3] = x[3] + interp<T>(hi, true, oy, oz);
 }
 
 // Exact zero-mean solve on the coarsest level (NC^3 points) in double with the
@@ -361,7 +381,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<T> A) {
         smooth8<T>(A, S, l8, x8, b8, w8, true);
         restrict8<T>(A, S, l8, x8, b8, w8);  // lane i of the first wave wrote what it reads next
         coarsest4<T>(S.h[0], S.h[1], S.q, S.lam);
-        if (i < 512) x8 += prolong8<T>(S.h[1]);
+        if (i < 512) x8 = x8 + prolong8<T>(S.h[1]);
         smooth8<T>(A, S, l8, x8, b8, w8, false);
         if constexpr (HAS16) {
             // the copy the last step did not read
