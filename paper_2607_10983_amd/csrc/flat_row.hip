@@ -1513,13 +1513,14 @@ constexpr int kRrTarget = 512;
 // Longest z chunks that still give one block of kLdsWaves waves per CU: the
 // outer kernel is bound by its bytes, and a chunk re-reads its two halo planes
 // (256^3: chunks of 32 planes 103.6 us against 107.8 us for 16; 16-wave
-// blocks measured slower).  Down to 4 planes where the level is small: with
+// blocks measured slower).  Down to 2 planes where the level is small: with
 // at least 16 the 64^3 level ran 32 blocks and the 128^3 level 128 (64^3
-// double 15.4 -> 6.9 us, 128^3 float 20.2 -> 15.5 us a launch).
+// double 15.4 -> 5.8 us, 128^3 float 20.2 -> 15.5 us a launch; two blocks per
+// CU at 128^3 16.4).
 void outer_lds_shape(int n, int waves, int& nz, int& nyb, int& blocks) {
     nyb = n / waves;
     nz = n;
-    while (nz > 4 && nyb * (n / nz) < 256) nz >>= 1;
+    while (nz > 2 && nyb * (n / nz) < 256) nz >>= 1;
     blocks = nyb * (n / nz);
 }
 
@@ -1713,7 +1714,8 @@ hipError_t launch_smooth_fromb_row(int n, double ih2, const T* b, T* out, double
 // 38.0 ms).  The pass from zero picks its own block by row size.
 constexpr int kPairWavesDefault = 8;
 constexpr size_t kPairLdsBudget = 64 * 1024;
-constexpr int kPairUnrollNz = 8;  // chunk height of the fully unrolled two-step variant
+constexpr int kPairUnrollNz = 8;  // chunk heights of the fully unrolled two-step variants
+constexpr int kPairUnrollNzSmall = 4;  // (64^3: from zero 5.8 -> 4.9 us in double)
 // Prefetch depth of the two-step kernel: two planes ahead for 2 KB rows,
 // whose blocks run one per CU (512^3 float 541 -> 498 us per launch); one
 // plane for smaller rows, where the extra registers cost occupancy (256^3
@@ -1741,6 +1743,7 @@ bool pair_kernels_apply(int n, size_t elem) {
     do {                                                                                         \
         if (pf2) MG_PAIR1(PREV1, Y1OUT, FROMB, true, 0, PREVB);                                  \
         else if (nz == kPairUnrollNz) MG_PAIR1(PREV1, Y1OUT, FROMB, false, kPairUnrollNz, PREVB); \
+        else if (nz == kPairUnrollNzSmall) MG_PAIR1(PREV1, Y1OUT, FROMB, false, kPairUnrollNzSmall, PREVB); \
         else MG_PAIR1(PREV1, Y1OUT, FROMB, false, 0, PREVB);                                     \
     } while (0)
 #define MG_PAIR(PREV1, Y1OUT, FROMB) MG_PAIRB(PREV1, Y1OUT, FROMB, false)
@@ -1767,6 +1770,9 @@ hipError_t launch_pair_nw(int n, double ih2, const T* x, const T* xp, const T* b
                 if (!pf2 && nz == kPairUnrollNz) {
                     if (y1 == nullptr) MG_PAIR1(false, false, true, true, kPairUnrollNz, false);
                     else MG_PAIR1(false, true, true, true, kPairUnrollNz, false);
+                } else if (!pf2 && nz == kPairUnrollNzSmall) {
+                    if (y1 == nullptr) MG_PAIR1(false, false, true, true, kPairUnrollNzSmall, false);
+                    else MG_PAIR1(false, true, true, true, kPairUnrollNzSmall, false);
                 } else if (y1 == nullptr) MG_PAIR(false, false, true);
                 else MG_PAIR(false, true, true);
             } else if (xp == nullptr && y1 == nullptr) {
@@ -1919,7 +1925,10 @@ hipError_t launch_smooth_pair_row(int n, double ih2, const T* x, const T* xp, co
 
 // Three-step kernel: 12 waves (8 output rows) per block, chunks of
 // kTripleNz planes; rows of at most 1 KB (float n <= 256, double n <= 128).
+// 64^3: 8 waves and chunks of kTripleNzSmall planes (double 7.0 -> 5.3 us; at 128^3 the shorter chunks were
+// slower, double 16.8 -> 21.3).
 constexpr int kTripleNz = 8;
+constexpr int kTripleNzSmall = 4;
 // z chunk of the fused post-smoothing pass in 12-wave blocks from 256^3: 16
 // planes.  Below 256^3 the chunk is kTripleNz.  A chunk forms step 0 on
 // NZC + 4 planes for NZC outputs, and each plane costs a barrier round
@@ -1939,11 +1948,12 @@ template <typename T, int NW>
 hipError_t launch_triple_nw(int n, double ih2, const T* x, const T* b, T* y3, double a0, double cd0, double a1,
                             double cd1, double a2, double cd2, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     constexpr int W = NW - 4;
+    constexpr int NZ = NW == 8 ? kTripleNzSmall : kTripleNz;
     const int nyb = (n + W - 1) / W;
-    const int blocks = nyb * (n / kTripleNz);
+    const int blocks = nyb * (n / NZ);
     DISPATCH_VEC(n, {
         if constexpr (64 * VEC * sizeof(T) <= 1024)
-            MG_LAUNCH((k_smooth3_lds<T, VEC, NW, kTripleNz>), dim3(blocks), dim3(64 * NW), s, ev0, ev1, n, (T)ih2, x,
+            MG_LAUNCH((k_smooth3_lds<T, VEC, NW, NZ>), dim3(blocks), dim3(64 * NW), s, ev0, ev1, n, (T)ih2, x,
                       b, y3, (T)a0, (T)cd0, (T)a1, (T)cd1, (T)a2, (T)cd2, nyb);
     })
     return hipGetLastError();
