@@ -369,8 +369,9 @@ mg_status smooth_level(mg_ctx* c, int l, bool from_zero, const T* pro_e = nullpt
     const int v = (int)L.a.size();
     // the last two steps of the pass run as one two-step kernel where it exists
     const bool pairs = c->use_pairs && L.x[2] != nullptr && !c->var;
-    // 19-point: the last two Chebyshev steps of the pass run as one kernel
-    const bool vpairs = c->use_pairs && c->var && cheb && L.x[2] != nullptr;
+    // 19-point: the last two Chebyshev steps of the pass run as one kernel, Jacobi steps two by two
+    // (no x_prev, so no third buffer)
+    const bool vpairs = c->use_pairs && c->var && var_pair_applies(L.n, sizeof(T)) && (!cheb || L.x[2] != nullptr);
     bool prev_b = false;  // x_{k-1} is the pointwise first step c0 D^-1 b, formed by the next kernel
     for (int k = 0; k < v; ++k) {
         double bytes = 0.0;
@@ -406,7 +407,7 @@ mg_status smooth_level(mg_ctx* c, int l, bool from_zero, const T* pro_e = nullpt
         const bool pro_pair = k == 0 && pro_e != nullptr && pairs && rem >= 2 && post_pair_fused(c, l, sizeof(T));
         const bool pair = pro_pair || (pairs && rem >= 2 && rem % 2 == 0 && !(k == 0 && from_zero) &&
                                        !(need_y1 && has_prev));
-        const bool vpair = vpairs && rem == 2 && !(k == 0 && from_zero);
+        const bool vpair = vpairs && (rem == 2 || (!cheb && rem % 2 == 0)) && !(k == 0 && from_zero);
         if (k == 0 && pro_e != nullptr && !pair) return MG_ERR_INVALID;
         const int kind = triple3                               ? MG_TIME_TRIPLE
                          : (pair || triple || vpair) && !fromb ? MG_TIME_PAIR
