@@ -346,6 +346,15 @@ inline bool post_pair_fused(const mg_ctx* c, int l, size_t elem) {
            pair_pro_applies(L.n, elem);
 }
 
+// Level l's post-smoothing pass starts with a 19-point step that forms x + P e
+// itself; a Chebyshev pass of several steps keeps that iterate, as the next
+// step's x_prev, in the third buffer.
+inline bool post_step_fused(const mg_ctx* c, int l, size_t elem) {
+    const Level& L = c->lev[l];
+    const bool keep = c->p.smoother == MG_CHEBYSHEV && L.a.size() > 1;
+    return c->use_pairs && c->var && var_pro_applies(L.n, elem) && (!keep || L.x[2] != nullptr);
+}
+
 // Level l runs its pass from zero as one three-step kernel (first step formed
 // from b on the fly): seven-point operator, two-step kernels available, and
 // at least three steps per pass.
@@ -353,8 +362,9 @@ inline bool from_zero_triple(const mg_ctx* c, int l) {
     return c->use_pairs && !c->var && c->lev[l].x[2] != nullptr && c->lev[l].a.size() >= 3;
 }
 
-// pro_e (not from zero): the pass starts from x + P pro_e, formed by its
-// first pair (post_pair_fused), instead of a prolongation launch.
+// pro_e (not from zero): the pass starts from x + P pro_e, formed by its first
+// pair (post_pair_fused) or step (post_step_fused), instead of a prolongation
+// launch.
 template <typename T>
 mg_status smooth_level(mg_ctx* c, int l, bool from_zero, const T* pro_e = nullptr) {
     Level& L = c->lev[l];
@@ -407,8 +417,9 @@ mg_status smooth_level(mg_ctx* c, int l, bool from_zero, const T* pro_e = nullpt
         const bool pro_pair = k == 0 && pro_e != nullptr && pairs && rem >= 2 && post_pair_fused(c, l, sizeof(T));
         const bool pair = pro_pair || (pairs && rem >= 2 && rem % 2 == 0 && !(k == 0 && from_zero) &&
                                        !(need_y1 && has_prev));
-        const bool vpair = vpairs && (rem == 2 || (!cheb && rem % 2 == 0)) && !(k == 0 && from_zero);
-        if (k == 0 && pro_e != nullptr && !pair) return MG_ERR_INVALID;
+        const bool vpro = k == 0 && pro_e != nullptr && post_step_fused(c, l, sizeof(T));
+        const bool vpair = vpairs && !vpro && (rem == 2 || (!cheb && rem % 2 == 0)) && !(k == 0 && from_zero);
+        if (k == 0 && pro_e != nullptr && !pair && !vpro) return MG_ERR_INVALID;
         const int kind = triple3                               ? MG_TIME_TRIPLE
                          : (pair || triple || vpair) && !fromb ? MG_TIME_PAIR
                                                                : MG_TIME_STEP;
@@ -457,6 +468,14 @@ mg_status smooth_level(mg_ctx* c, int l, bool from_zero, const T* pro_e = nullpt
             prev = mid;
             cur = out;
             k = 2;  // three steps done
+        } else if (vpro) {  // x, e -> x_1 and, where the next step needs it, x_0 = x + P e
+            const int out = other(cur);
+            const int keep = cheb && v > 1 ? 3 - cur - out : -1;
+            HIPCHK(c, launch_var_pro<T, T>(L.n, L.ih2, op.coeff, bufs[cur], pro_e, (const T*)L.b, bufs[out],
+                                           keep >= 0 ? bufs[keep] : nullptr, L.a[0], L.c[0], c->stream, ev0, ev1));
+            bytes = (3.0 + 1.0 / 8.0 + (keep >= 0 ? 1.0 : 0.0)) * fbytes + cbytes;  // x, e, b, C; x_1, [x_0]
+            prev = keep;
+            cur = out;
         } else if (vpair) {  // x, x_prev -> y2 in the third buffer (the kernel reads both on halo rows)
             const T* xp = has_prev ? bufs[prev] : nullptr;
             const int out = has_prev ? 3 - cur - prev : other(cur);
@@ -651,8 +670,8 @@ mg_status post_level(mg_ctx* c, int l) {
         // x, b read, x_3 written, e read once per coarse point
         return time_end(c, fine, MG_TIME_TRIPLE, (3.0 + 1.0 / 8.0) * (double)L.N * sizeof(T));
     }
-    // the prolongation runs inside the pass's first pair
-    if (post_pair_fused(c, l, sizeof(T)))
+    // the prolongation runs inside the pass's first pair or step
+    if (post_pair_fused(c, l, sizeof(T)) || post_step_fused(c, l, sizeof(T)))
         return smooth_level<T>(c, l, false, (const T*)Lc.x[Lc.cur]);
     if ((st = time_events(c, fine, MG_TIME_TRANSFER, &ev0, &ev1)) != MG_OK) return st;
     HIPCHK(c, launch_prolong_add<T>(L.n, (const T*)Lc.x[Lc.cur], (T*)L.x[L.cur], c->stream, ev0, ev1));
@@ -953,9 +972,10 @@ void layout(mg_ctx* c, int source, Arena& keep, Arena& tmp, SetupMem& sm) {
         L.ih2 = 1.0 / (L.h * L.h);
         L.x[0] = keep.take(L.N * Tsz);
         L.x[1] = keep.take(L.N * Tsz);
-        const bool third = c->use_pairs && (c->var ? var_pair_applies(L.n, Tsz) && p.smoother == MG_CHEBYSHEV &&
-                                                         p.cheb_degree >= 2
-                                                   : pair_kernels_apply(L.n, Tsz));
+        const bool third =
+            c->use_pairs && (c->var ? (var_pair_applies(L.n, Tsz) || var_pro_applies(L.n, Tsz)) &&
+                                          p.smoother == MG_CHEBYSHEV && p.cheb_degree >= 2
+                                    : pair_kernels_apply(L.n, Tsz));
         L.x[2] = third ? keep.take(L.N * Tsz) : nullptr;
         L.b = keep.take(L.N * Tsz);
         L.coeff = c->var ? keep.take(6 * L.N * Tsz) : nullptr;

@@ -27,6 +27,13 @@ template <typename T, typename TC>
 hipError_t launch_var_smooth_pair(int n, double ih2, const TC* C, const T* x, const T* xp, const T* b, T* y2,
                                   double a1, double c1, double a2, double c2, hipStream_t s, hipEvent_t ev0,
                                   hipEvent_t ev1);
+// The first step of a pass from x0 = x + P e: out = x0 + a x0 + c D^-1 (b - M x0),
+// and x0 itself into x0out (may be nullptr).  out and x0out differ from x.
+// Levels for which var_pro_applies; hipErrorInvalidValue otherwise.
+bool var_pro_applies(int n, size_t elem);
+template <typename T, typename TC>
+hipError_t launch_var_pro(int n, double ih2, const TC* C, const T* x, const T* e, const T* b, T* out, T* x0out,
+                          double a, double c, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 // out = b - M x (b != nullptr) or out = M x
 template <typename T, typename TC>
 hipError_t launch_var_resid_row(int n, double ih2, const TC* C, const T* x, const T* b, T* out, hipStream_t s,

@@ -18,6 +18,7 @@
 // D = -sum_a (f_a+ + f_a-) / h^2 its diagonal.
 #include "var_row.h"
 
+#include "flat_rows.h"
 #include "fma.h"
 #include "launch.h"
 #include "row.h"
@@ -464,6 +465,101 @@ __global__ __launch_bounds__(64 * W) void k_var_smooth_lds(int n, T ih2, const T
         }
         strow<T, VEC>(out + r, o);
         if (more) ring_shift<T, VEC, W>(rg, U, hr, xn, hn);
+        cq_shift<ZQ, T, VEC>(q);
+    }
+}
+
+// The first step of a post-smoothing pass with the prolongation in front:
+//   x0 = x + P e,  out = x0 + a x0 + c D^-1 (b - M x0)
+// The rows of x0 are formed as they are loaded (each once per block and plane,
+// the block's halo rows twice) and go through the same ring; x0out (may be
+// null) receives them as the next step's x_prev.  Rounding of the prolongation
+// as in k_prolong_row and of the step as in k_var_smooth_lds: same bits.
+template <typename T, typename TC, int VEC, int W>
+__global__ __launch_bounds__(64 * W) void k_var_pro_lds(int n, T ih2, const TC* __restrict__ C,
+                                                        const T* __restrict__ x, const T* __restrict__ ec,
+                                                        const T* __restrict__ b, T* __restrict__ out,
+                                                        T* __restrict__ x0out, T a, T c, int nz, int nyb) {
+    constexpr int NR = 64 * VEC;
+    constexpr size_t N = (size_t)NR * NR * NR;
+    constexpr bool ZQ = true;
+    __shared__ T ring[4][W + 2][NR];
+    const RowGrid g{NR, NR - 1}, gc{NR / 2, NR / 2 - 1};
+    const int lb = xcd_logical(blockIdx.x, gridDim.x);
+    const int yb = lb % nyb, zc = lb / nyb;
+    const int w = wave_id();
+    const int y0 = yb * W, y = y0 + w;
+    const int z0 = zc * nz;
+    const int lane = threadIdx.x & 63;
+    const size_t off = (size_t)lane * VEC;
+    const bool lo = w == 0, hi = w == W - 1;
+    const int yh = lo ? y0 - 1 : y0 + W;  // halo row of the edge waves
+    const Ring<T, VEC, W> rg{ring, w, lo ? 0 : W + 1, lane, lo || hi};
+    struct Raw {  // a row of x and the coarse rows it takes, as loaded
+        T v[VEC];
+        CoarseRows<T, VEC> c;
+    };
+    auto load = [&](Raw& r, int yy, int z) {
+        ldrow<T, VEC>(r.v, x + g.row(yy, z) + off);
+        coarse_load<T, VEC>(r.c, ec, gc, yy, z, lane);
+    };
+    auto form = [&](T (&v)[VEC], Raw& r, int yy, int z) {
+        prolong_add<T, VEC>(r.v, r.c, yy, z);
+        copyrow(v, r.v);
+    };
+    T U[3][3][VEC], hr[VEC] = {}, xn[VEC], hn[VEC];
+    {
+        Raw r[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) load(r[k], y, z0 - 1 + k);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) form(U[1][k], r[k], y, z0 - 1 + k);
+        lds_strow<T, VEC>(rg.row(z0 - 1, w + 1), lane, U[1][0]);
+        lds_strow<T, VEC>(rg.row(z0, w + 1), lane, U[1][1]);
+        if (rg.edge) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) load(r[k], yh, z0 - 1 + k);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                form(hr, r[k], yh, z0 - 1 + k);
+                if (k < 2) lds_strow<T, VEC>(rg.row(z0 - 1 + k, rg.hs), lane, hr);
+            }
+        }
+    }
+    CQueue<T, VEC> q;
+    cq_load<ZQ, T, TC, VEC>(q, 0, C, N, g, y, z0 - 1, off);
+    cq_load<ZQ, T, TC, VEC>(q, 1, C, N, g, y, z0, off);
+    for (int k = 0; k < nz; ++k) {
+        const int z = z0 + k;
+        const bool more = k + 1 < nz;
+        Raw xr, hw;
+        if (more) {  // the plane after next, one iteration early
+            load(xr, y, z + 2);
+            if (rg.edge) load(hw, yh, z + 2);
+        }
+        ring_publish<T, VEC, W>(rg, U, hr, z);
+        cq_load<ZQ, T, TC, VEC>(q, 2, C, N, g, y, z + 1, off);
+        CRows<T, VEC> cr;
+        if constexpr (kVarCrowsEarly) cr_load<T, TC, VEC>(cr, C, N, g, y, z, off);
+        T bb[VEC], Mu[VEC], D[VEC], o[VEC];
+        const size_t r = g.row(y, z) + off;
+        ldrow<T, VEC>(bb, b + r);
+        __syncthreads();
+        ring_gather<T, VEC, W>(rg, U, z);
+        if constexpr (!kVarCrowsEarly) cr_load<T, TC, VEC>(cr, C, N, g, y, z, off);
+        var19_row_c<ZQ, T, TC, VEC>(U, q, cr, C, N, g, y, z, off, ih2, Mu, D);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const T xc = U[1][1][e];
+            o[e] = xc + a * (xc - T(0)) + c * (bb[e] - Mu[e]) / D[e];
+        }
+        strow<T, VEC>(out + r, o);
+        if (x0out) strow<T, VEC>(x0out + r, U[1][1]);
+        if (more) {
+            form(xn, xr, y, z + 2);
+            if (rg.edge) form(hn, hw, yh, z + 2);
+            ring_shift<T, VEC, W>(rg, U, hr, xn, hn);
+        }
         cq_shift<ZQ, T, VEC>(q);
     }
 }
@@ -988,6 +1084,32 @@ hipError_t launch_var_smooth_pair(int n, double ih2, const TC* C, const T* x, co
     return hipGetLastError();
 }
 
+// The step with the prolongation in front: rows of up to 1 KB, as the fused
+// residual and restriction (longer rows do not leave registers for the coarse
+// rows).  Against the prolongation and the step: float 256^3 150 -> 139 us,
+// 128^3 19.3 -> 16.6, 64^3 8.7 -> 5.4; double 128^3 35.4 -> 31.4, 64^3
+// 13.0 -> 7.0 (a 64^3 moving-mesh step 1004 -> 936 us).
+bool var_pro_applies(int n, size_t elem) { return var_row_kernels_apply(n) && (size_t)n * elem <= 1024; }
+
+template <typename T, typename TC>
+hipError_t launch_var_pro(int n, double ih2, const TC* C, const T* x, const T* e, const T* b, T* out, T* x0out,
+                          double a, double c, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    if (!var_pro_applies(n, sizeof(T)) || !x || !e || out == x || x0out == x || x0out == out)
+        return hipErrorInvalidValue;
+    constexpr int W = kVarLdsWaves;
+    const int nyb = n / W;
+    int nz = n;
+    while (nz > (n < 128 ? 2 : 4) && nyb * (n / nz) < 1024) nz >>= 1;
+    DISPATCH_VEC(n, {
+        if constexpr (64 * VEC * sizeof(T) <= 1024)
+            MG_LAUNCH((k_var_pro_lds<T, TC, VEC, W>), dim3(nyb * (n / nz)), dim3(64 * W), s, ev0, ev1, n, (T)ih2, C, x,
+                      e, b, out, x0out, (T)a, (T)c, nz, nyb);
+        else
+            return hipErrorInvalidValue;
+    })
+    return hipGetLastError();
+}
+
 template <typename T, typename TC>
 hipError_t launch_var_resid_row(int n, double ih2, const TC* C, const T* x, const T* b, T* out, hipStream_t s,
                                 hipEvent_t ev0, hipEvent_t ev1) {
@@ -1074,6 +1196,8 @@ hipError_t launch_var_outer_row(int n, double ih2, const TC* C, const double* ph
                                                       hipEvent_t);                                                 \
     template hipError_t launch_var_resid_row<T, TC>(int, double, const TC*, const T*, const T*, T*, hipStream_t,   \
                                                     hipEvent_t, hipEvent_t);                                       \
+    template hipError_t launch_var_pro<T, TC>(int, double, const TC*, const T*, const T*, const T*, T*, T*,        \
+                                              double, double, hipStream_t, hipEvent_t, hipEvent_t);                \
     template hipError_t launch_var_rr<T, TC>(int, double, const TC*, const T*, const T*, T*, const T*, T*, double, \
                                              hipStream_t, hipEvent_t, hipEvent_t);
 INST_VAR(float, float)
