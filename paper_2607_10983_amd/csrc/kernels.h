@@ -36,12 +36,12 @@ hipError_t launch_smooth_step(const OpDesc<TC>& op, const T* x, const T* xprev, 
                               hipEvent_t ev1 = nullptr);
 
 // ---- residual + full-weighting restriction ---------------------------------
-// coarse = R(b - M x) on the (n/2)^3 grid; x == nullptr means x = 0.  When the
-// fused row kernel does not apply and `scratch` (n^3 elements, distinct from
-// x, b and coarse) is given, the residual is formed there first and then
-// restricted (two passes); without scratch a fused gather kernel is used.
-// first (19-point, two-pass form): the restriction also writes the coarse
-// level's first smoothing step from zero, first.x1 = first.c0 coarse / D.
+// coarse = R(b - M x) on the (n/2)^3 grid; x == nullptr means x = 0.  Where no
+// fused row kernel applies and `scratch` (n^3 elements, distinct from x, b and
+// coarse) is given, the residual is formed there first and then restricted
+// (two passes); without scratch a fused gather kernel is used.
+// first (19-point; not the gather kernel): the restriction also writes the
+// coarse level's first smoothing step from zero, first.x1 = first.c0 coarse / D.
 template <typename T>
 struct FirstStep {
     const T* C = nullptr;  // coarse coefficients

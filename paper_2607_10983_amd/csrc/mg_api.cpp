@@ -348,11 +348,16 @@ inline bool post_pair_fused(const mg_ctx* c, int l, size_t elem) {
 
 // Level l's post-smoothing pass starts with a 19-point step that forms x + P e
 // itself; a Chebyshev pass of several steps keeps that iterate, as the next
-// step's x_prev, in the third buffer.
+// step's x_prev, in the third buffer.  Not where the whole pass runs in pairs
+// on rows of 1 KB: at 256^3 float the prolongation and a pair take 27 + 197 us,
+// this step and a single one 141 + 127 to 137 (128^3: 5 + 30 and 17 + 15).
 inline bool post_step_fused(const mg_ctx* c, int l, size_t elem) {
     const Level& L = c->lev[l];
-    const bool keep = c->p.smoother == MG_CHEBYSHEV && L.a.size() > 1;
-    return c->use_pairs && c->var && var_pro_applies(L.n, elem) && (!keep || L.x[2] != nullptr);
+    const bool cheb = c->p.smoother == MG_CHEBYSHEV;
+    const size_t v = L.a.size();
+    const bool paired = var_pair_applies(L.n, elem) && (size_t)L.n * elem >= 1024 && (cheb ? v == 2 : v % 2 == 0);
+    return c->use_pairs && c->var && var_pro_applies(L.n, elem) && !paired &&
+           (!cheb || v == 1 || L.x[2] != nullptr);
 }
 
 // Level l runs its pass from zero as one three-step kernel (first step formed
