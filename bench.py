@@ -45,15 +45,15 @@ HBM_PEAK_GBPS = 8000.0
 # is the one the counters were taken on.  Keys are the first name of each
 # kind's label (kernel_name).
 TRAFFIC = {
-    "device_code_sha256": "d54b7c1db8381bea087ed9da4386c84b2e3358a5ea13b709a8386296b1ca3cd6",
+    "device_code_sha256": "f405c6b10618a8b965e5de926cb6583de8e82678b4473398087915bfd16d551f",
     "bytes_per_launch": {
         # the benchmark step: outer (with the first-cycle variant), pass from
         # zero (b -> x3), prolongation + three steps, residual + restriction
-        (256, 3): {"k_outer_lds": 536855684, "k_smooth2_lds": 151742958, "k_smooth3p_lds": 238153913,
-                   "k_rr_row": 159429926},
+        (256, 3): {"k_outer_lds": 536899603, "k_smooth2_lds": 150329862, "k_smooth3p_lds": 238161601,
+                   "k_rr_row": 159425548},
         # the 512^3 leg: step from b, the three pairs, outer, residual + restriction (k_rr_lds)
-        (512, 4): {"k_smooth_row": 1137164769, "k_smooth2_lds": 2278180068, "k_outer_lds": 4445624636,
-                   "k_rr_row": 1196833543},
+        (512, 4): {"k_smooth_row": 1137234727, "k_smooth2_lds": 2279472168, "k_outer_lds": 4465101552,
+                   "k_rr_row": 1196476359},
     },
 }
 
@@ -61,39 +61,36 @@ TRAFFIC = {
 def measured_traffic(n, degree, kernel):
     import hashlib
     csrc = os.path.join(ROOT, "paper_2607_10983_amd", "csrc")
-    dev = "".join(open(os.path.join(csrc, f)).read() for f in ("flat_row.hip", "fma.h", "row.h"))
+    dev = "".join(open(os.path.join(csrc, f)).read() for f in ("flat_row.hip", "flat_rows.h", "fma.h", "row.h"))
     if hashlib.sha256(dev.encode()).hexdigest() != TRAFFIC["device_code_sha256"]:
         return None
     v = TRAFFIC["bytes_per_launch"].get((n, degree), {}).get(kernel)
     return round(v) if v is not None else None
 
 
-def pass_bytes(v, from_zero, pairs, triple, s, rowk=False):
+def pass_bytes(v, from_zero, pairs, triple, s, pro=False):
     """Algorithmic bytes per point of one smoothing pass of degree v, following
     the library's schedule: a pass from zero of degree 4 is one kernel for
     steps 0 and 1 (b -> x2) and a pair that forms x_prev = x1 from b
     (x2, b -> x4); other passes from zero start with one kernel for their
     first three steps (b -> x3, and x2 when a fourth step needs it as x_prev);
-    on row-kernel levels without two-step kernels (rowk) a pass from zero of
-    at least three steps starts with steps 0 and 1 from b (b -> x2) and a
-    step that forms x_prev from b (x2, b -> x3); a pass of three steps from a
-    nonzero iterate is one three-step kernel (x, b -> x3); otherwise steps
-    pair up from the end of the pass where the two-step kernel runs (a pair
-    that is not the last writes its first step)."""
+    a pass of three steps from a nonzero iterate is one three-step kernel
+    (x, b -> x3); otherwise steps pair up from the end of the pass where the
+    two-step kernel runs (a pair that is not the last writes its first step).
+    pro: the pass starts with a pair that prolongs, whatever its degree."""
     if not from_zero and triple and v == 3:
         return 3 * s
     if from_zero and pairs and v == 4:
         return (2 + 3) * s
     tot, prev, k = 0.0, False, 0
-    if from_zero and not pairs and rowk and v >= 3:
-        tot, prev, k = (2 + 3) * s, True, 3
     if from_zero and pairs and v >= 3:
         tot += (2 + (v > 3)) * s
         prev, k = v > 3, 3
     while k < v:
         rem = v - k
         need_y1 = rem > 2
-        if pairs and rem >= 2 and rem % 2 == 0 and not (k == 0 and from_zero) and not (need_y1 and prev):
+        if (k == 0 and pro) or (pairs and rem >= 2 and rem % 2 == 0 and not (k == 0 and from_zero)
+                                and not (need_y1 and prev)):
             tot += (3 + prev + need_y1) * s
             prev, k = need_y1, k + 2
         elif k == 0 and from_zero:
@@ -108,41 +105,41 @@ def pass_bytes(v, from_zero, pairs, triple, s, rowk=False):
 def model_bytes_per_cycle(n, levels, degree, precision):
     """Algorithmic bytes of one outer iteration (inner V-cycle + outer residual/update),
     every field element each kernel reads or writes counted once, following the
-    library's schedule: multi-step kernels on levels 64 <= n_l (two-step rows up
-    to 2 KB, three-step rows up to 1 KB; from 128^3 the three-step pass, and
-    on rows over 1 KB the first pair of an even-degree pass, forms x + P e
-    itself, so the prolongation writes nothing), the 32^3 and 64^3
-    levels of a float hierarchy as two fused visits each, the outer kernel
-    writing the first step from zero only where the fine level has no
-    pass-from-zero kernel (rows of more than 1024 points or degree below 3)."""
+    library's schedule: two-step kernels on levels 64 <= n_l <= 1024 and
+    three-step kernels on rows up to 1 KB; from 128^3 the three-step pass, and
+    on rows over 1 KB the first pair of a pass, forms x + P e itself, so the
+    prolongation writes nothing; the 32^3 level and a float hierarchy's 64^3
+    level as two fused visits each (up to degree 4; the pre visit of 64^3 up to
+    3); the outer kernel writing the first step from zero only where the fine
+    level has no pass-from-zero kernel (degree below 3)."""
     s = 8 if precision == "fp64" else 4
     tot = 0.0
     tail_start = next((l for l in range(levels) if n >> l <= 16), levels)
+    x1_outer = False
     for l in range(levels - 1):
         nl = n >> l
-        pairs = 64 <= nl <= 1024 and nl * s <= 2048
-        triple = 64 <= nl and nl * s <= 1024
-        if precision != "fp64" and nl in (32, 64) and degree <= 3 and l != tail_start:
-            tot += nl ** 3 * ((2 * s + s / 8) + (3 * s + s / 8))  # fused pre and post visits
-            continue
-        rowk = 64 <= nl <= 1024
-        x1_outer = l == 0 and not (rowk and degree >= 3)
-        pre = pass_bytes(degree, True, pairs, triple, s, rowk) - (2 * s if x1_outer else 0)  # step 0 by the outer
-        post = pass_bytes(degree, False, pairs, triple, s)
-        # the prolongation runs inside the post-smoothing pass's first kernel:
-        # the three-step pass from 128^3 (degree 3), the first pair on split
-        # rows (rows of 1-2 KB, an even degree), the first two single steps on
-        # rows over 2 KB (x, e, b -> x1; x1, x, e, b -> x2: e read twice)
-        step_pro = rowk and nl * s > 2048 and degree >= 2
-        fused_prolong = ((triple and nl >= 128 and degree == 3) or (pairs and nl * s > 1024 and degree % 2 == 0)
-                         or step_pro)
-        if step_pro:
-            post = (3 + 4 + 4 * (degree - 2)) * s + s / 8
-        transfers = 2 * s + s / 8 + (s / 8 if fused_prolong else 2 * s + s / 8)
-        tot += nl ** 3 * (pre + post + transfers)
+        pairs = 64 <= nl <= 1024
+        triple = pairs and nl * s <= 1024
+        visits = l != tail_start and degree <= 4 and (nl == 32 or (nl == 64 and s == 4))
+        pre_visit = visits and (nl == 32 or degree <= 3)
+        rr = 2 * s + s / 8
+        if pre_visit:
+            down = 2 * s + s / 8
+        else:
+            down = pass_bytes(degree, True, pairs, triple, s) + rr
+            if l == 0 and not (pairs and degree >= 3):
+                x1_outer = True
+                down -= 2 * s  # step 0 by the outer
+        if visits:
+            up = 3 * s + s / 8
+        else:
+            # the prolongation runs inside the post-smoothing pass's first kernel
+            pro = pairs and nl * s > 1024 and degree >= 2
+            fused = pro or (triple and nl >= 128 and degree == 3)
+            up = pass_bytes(degree, False, pairs, triple, s, pro) + (s / 8 if fused else 2 * s + s / 8)
+        tot += nl ** 3 * (down + up)
     # outer: read phi, e, b; write phi, r (and the first smoothing step where no pass-from-zero kernel runs)
-    fine_rowk = 64 <= n <= 1024
-    tot += n ** 3 * (8 + s + 8 + 8 + s + (0 if fine_rowk and degree >= 3 else s))
+    tot += n ** 3 * (8 + s + 8 + 8 + s + (s if x1_outer else 0))
     return tot
 
 
@@ -177,14 +174,15 @@ KINDS = (MG_TIME_STEP, MG_TIME_PAIR, MG_TIME_TRIPLE, MG_TIME_OUTER, MG_TIME_TRAN
 def kernel_name(kind, n, precision, var=False):
     t = "double" if precision == "fp64" else "float"
     if var:
-        return {MG_TIME_STEP: f"k_var_smooth_row / k_var_smooth_lds (fine-level 19-point Chebyshev step, {t})",
+        return {MG_TIME_STEP: f"k_var_smooth_row / k_var_smooth_lds / k_var_pro_lds (fine-level 19-point step, {t})",
                 MG_TIME_PAIR: f"k_var_smooth2_lds (fine-level 19-point two-step pass, {t})",
                 MG_TIME_OUTER: "k_var_outer_row (19-point outer defect correction: phi += e, FP64 residual, norms)",
-                MG_TIME_TRANSFER: f"k_var_resid_row / k_var_resid_lds / k_prolong_row (fine-level 19-point "
-                                  f"residual, prolongation, {t})",
+                MG_TIME_TRANSFER: f"k_var_rr_lds / k_var_resid_row / k_var_resid_lds / k_prolong_row (fine-level "
+                                  f"19-point residual + restriction, prolongation, {t})",
                 }.get(kind, f"kind {kind}")
     return {MG_TIME_STEP: f"k_smooth_row / k_smooth_lds (fine-level single Chebyshev step, {t})",
-            MG_TIME_PAIR: f"k_smooth2_lds (fine-level two-step pass and pass from zero, {t})",
+            MG_TIME_PAIR: f"k_smooth2_lds / k_smooth2x_lds / k_pair_tile (fine-level two-step pass and pass from zero, "
+                          f"{t})",
             MG_TIME_TRIPLE: (f"k_smooth3p_lds (fine-level prolongation + three-step pass, {t})" if n >= 128
                              else f"k_smooth3_lds (fine-level three-step pass, {t})"),
             MG_TIME_OUTER: "k_outer_lds (outer defect correction: phi += e, FP64 residual r, norms, r cast "

@@ -84,7 +84,7 @@ enum mg_dtype {
 enum mg_option {
     MG_OPT_NO_PAIR = 1,        /* every smoothing step its own kernel (no two- or three-step passes,
                                   no prolongation fused into post-smoothing) */
-    MG_OPT_NO_VISIT = 2,       /* no fused visits of the 32^3 and 64^3 levels (seven-point float; 19-point 32^3) */
+    MG_OPT_NO_VISIT = 2,       /* no fused visits (seven-point 32^3, in float 64^3; 19-point 32^3) */
     MG_OPT_NO_TAIL = 4,        /* levels of at most 16^3 points as separate kernels, not one workgroup */
     MG_OPT_NO_FUSED_SUMS = 8,  /* outer residual norms finished by their own kernel */
     MG_OPT_GRAPH = 16,         /* coarse sub-cycle replayed from a captured HIP graph */
