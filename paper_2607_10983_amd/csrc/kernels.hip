@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kThreads) void k_outer_residual(int n, TA ih2, cons
                                                              TR* __restrict__ r, TR* __restrict__ x1, TA c0,
                                                              double* partials, int nz) {
     const double bmean = bm.get();
-    __shared__ double sh[kThreads];
+    __shared__ double sh[3 * kThreads];
     const Grid g{n, n - 1};
     const size_t N = (size_t)n * n * n;
     const int xi = blockIdx.x * blockDim.x + threadIdx.x;
@@ -227,13 +227,12 @@ __global__ __launch_bounds__(kThreads) void k_outer_residual(int n, TA ih2, cons
     }
     // three partial sums, arrays of the block count: sum (b - bmean)^2, sum r^2, sum phi
     const int nb = gridDim.x * gridDim.y * gridDim.z;
-    const double t0 = block_sum(sb, sh);
-    const double t1 = block_sum(ss, sh);
-    const double t2 = block_sum(sp, sh);
+    double t[3] = {sb, ss, sp};
+    block_sums<3>(t, sh);
     if (lin_tid() == 0) {
-        partials[lin_bid()] = t0;
-        partials[nb + lin_bid()] = t1;
-        partials[2 * nb + lin_bid()] = t2;
+        partials[lin_bid()] = t[0];
+        partials[nb + lin_bid()] = t[1];
+        partials[2 * nb + lin_bid()] = t[2];
     }
 }
 

@@ -65,7 +65,7 @@ template <typename TI, bool HASQ>
 __global__ __launch_bounds__(kThreads) void k_pcg_dots(int n, const double* __restrict__ r,
                                                        const TI* __restrict__ zv, const double* __restrict__ q,
                                                        double* partials, int nb, int nz) {
-    __shared__ double sh[kThreads];
+    __shared__ double sh[2 * kThreads];
     const Grid g{n, n - 1};
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y * blockDim.y + threadIdx.y;
@@ -77,11 +77,11 @@ __global__ __launch_bounds__(kThreads) void k_pcg_dots(int n, const double* __re
         rz += r[i] * zi;
         if constexpr (HASQ) zq += zi * q[i];
     }
-    const double t0 = block_sum(rz, sh);
-    const double t1 = block_sum(zq, sh);
+    double t[2] = {rz, zq};
+    block_sums<2>(t, sh);
     if (lin_tid() == 0) {
-        partials[lin_bid()] = t0;
-        partials[nb + lin_bid()] = t1;
+        partials[lin_bid()] = t[0];
+        partials[nb + lin_bid()] = t[1];
     }
 }
 
@@ -149,15 +149,16 @@ __global__ __launch_bounds__(kThreads) void k_pcg_update(int n, double* __restri
 
 __global__ __launch_bounds__(1024) void k_pcg_scalars(const double* __restrict__ partials, int nb,
                                                       double* scal, int which, int restart) {
-    __shared__ double sh[1024];
+    __shared__ double sh[2 * 1024];
     const int tid = threadIdx.x;
     double v0 = 0.0, v1 = 0.0;
     for (int i = tid; i < nb; i += 1024) {
         v0 += partials[i];
         if (which == kPcgBeta) v1 += partials[nb + i];
     }
-    const double s0 = block_sum(v0, sh);
-    const double s1 = block_sum(v1, sh);
+    double t[2] = {v0, v1};
+    block_sums<2>(t, sh);
+    const double s0 = t[0], s1 = t[1];
     if (tid != 0) return;
     if (which == kPcgBeta) {
         // flexible CG: beta = (z_k, r_k - r_{k-1}) / (z_{k-1}, r_{k-1}) with

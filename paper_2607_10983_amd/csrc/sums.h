@@ -38,7 +38,7 @@ struct Mean {
     __device__ __forceinline__ double get() const { return *sum * inv; }
 };
 
-// Every thread of the block calls it; sh holds kSumLanes doubles.
+// Every thread of the block (64 or more) calls it; sh holds kSumLanes doubles.
 __device__ __forceinline__ void finish_sums(const SumsJob& job, double* sh) {
     const int nt = blockDim.x * blockDim.y * blockDim.z;
     const int tid = threadIdx.x + blockDim.x * (threadIdx.y + blockDim.y * threadIdx.z);
@@ -50,13 +50,18 @@ __device__ __forceinline__ void finish_sums(const SumsJob& job, double* sh) {
             sh[v] = a;
         }
         __syncthreads();
-        for (int s = kSumLanes >> 1; s > 0; s >>= 1) {
+        int s = kSumLanes >> 1;
+        for (; s >= 64; s >>= 1) {
             for (int v = tid; v < s; v += nt) sh[v] += sh[v + s];
             __syncthreads();
         }
-        if (tid == 0) {
-            job.out[job.slot + k] = sh[0];
-            if (job.host_out) job.host_out[job.slot + k] = sh[0];
+        if (tid < 64) {  // the levels below one wave: the same pairs by cross-lane moves
+            double a = sh[tid];
+            for (; s > 0; s >>= 1) a += __shfl_down(a, s, 64);
+            if (tid == 0) {
+                job.out[job.slot + k] = a;
+                if (job.host_out) job.host_out[job.slot + k] = a;
+            }
         }
         __syncthreads();
     }
