@@ -54,8 +54,9 @@ struct TimingPair {
 };
 
 // Integer results of the setup kernels: bounds per level (bits of a double),
-// invalid cells per level from 16, invalid entries of the coarsest inverse at 32.
-constexpr int kSetupSlots = 33;
+// invalid cells per level from 16, invalid entries of the coarsest inverse at
+// 32, its elimination steps that met an indefinite block at 33.
+constexpr int kSetupSlots = 34;
 
 }  // namespace
 
@@ -208,6 +209,89 @@ void flat_basis(int nc, double hc, std::vector<double>& Q, std::vector<double>& 
     }
     for (int j = 0; j < nc; ++j) Q[j + nc * (nc - 1)] = (j % 2 ? -1.0 : 1.0) / std::sqrt((double)nc);
     lam[nc - 1] = eig(nc / 2);
+}
+
+// Dense matrix of the 19-point operator on the coarsest level (host, double).
+void assemble_dense(int n, double ih2, const std::vector<double>& C, std::vector<double>& M) {
+    const int N = n * n * n;
+    M.assign((size_t)N * N, 0.0);
+    auto id = [n](int x, int y, int z) { return (((z % n + n) % n) * n + ((y % n + n) % n)) * n + ((x % n + n) % n); };
+    auto cc = [&](int c, int x, int y, int z) { return C[(size_t)c * N + id(x, y, z)]; };
+    for (int z = 0; z < n; ++z)
+        for (int y = 0; y < n; ++y)
+            for (int x = 0; x < n; ++x) {
+                const int i = id(x, y, z);
+                const int p[3] = {x, y, z};
+                for (int a = 0; a < 3; ++a)
+                    for (int s = -1; s <= 1; s += 2) {
+                        int q[3] = {p[0], p[1], p[2]};
+                        q[a] += s;
+                        const double cf = 0.5 * (cc(a, x, y, z) + cc(a, q[0], q[1], q[2]));
+                        M[(size_t)i * N + id(q[0], q[1], q[2])] += cf * ih2;
+                        M[(size_t)i * N + i] -= cf * ih2;
+                    }
+                const int pa[3] = {0, 0, 1}, pb[3] = {1, 2, 2};
+                for (int k = 0; k < 3; ++k) {
+                    const int a = pa[k], b = pb[k], comp = 3 + k;
+                    for (int sa = -1; sa <= 1; sa += 2)
+                        for (int sb = -1; sb <= 1; sb += 2) {
+                            int qa[3] = {p[0], p[1], p[2]}, qb[3] = {p[0], p[1], p[2]}, q[3] = {p[0], p[1], p[2]};
+                            qa[a] += sa;
+                            qb[b] += sb;
+                            q[a] += sa;
+                            q[b] += sb;
+                            const double v = sa * sb * (cc(comp, qa[0], qa[1], qa[2]) + cc(comp, qb[0], qb[1], qb[2])) * 0.25 * ih2;
+                            M[(size_t)i * N + id(q[0], q[1], q[2])] += v;
+                        }
+                }
+            }
+}
+
+// Zero-mean pseudo-inverse of a symmetric M with null space span(1):
+// B = M - s 11^T / N is regular, and G = P B^-1 P with P = I - 11^T / N.
+// Eliminated with partial pivoting, so M need not be semidefinite.
+bool pseudo_inverse(int N, const std::vector<double>& M, std::vector<double>& G) {
+    double s = 0.0;
+    for (int i = 0; i < N; ++i) s += std::fabs(M[(size_t)i * N + i]);
+    s /= N;
+    std::vector<double> A((size_t)N * 2 * N, 0.0);
+    for (int i = 0; i < N; ++i) {
+        for (int j = 0; j < N; ++j) A[(size_t)i * 2 * N + j] = M[(size_t)i * N + j] - s / N;
+        A[(size_t)i * 2 * N + N + i] = 1.0;
+    }
+    const int W = 2 * N;
+    for (int col = 0; col < N; ++col) {  // Gauss-Jordan with partial pivoting
+        int piv = col;
+        for (int r = col + 1; r < N; ++r)
+            if (std::fabs(A[(size_t)r * W + col]) > std::fabs(A[(size_t)piv * W + col])) piv = r;
+        if (A[(size_t)piv * W + col] == 0.0) return false;
+        if (piv != col)
+            for (int j = 0; j < W; ++j) std::swap(A[(size_t)piv * W + j], A[(size_t)col * W + j]);
+        const double inv = 1.0 / A[(size_t)col * W + col];
+        for (int j = 0; j < W; ++j) A[(size_t)col * W + j] *= inv;
+        for (int r = 0; r < N; ++r) {
+            if (r == col) continue;
+            const double f = A[(size_t)r * W + col];
+            if (f == 0.0) continue;
+            for (int j = 0; j < W; ++j) A[(size_t)r * W + j] -= f * A[(size_t)col * W + j];
+        }
+    }
+    std::vector<double> Bi((size_t)N * N);
+    for (int i = 0; i < N; ++i)
+        for (int j = 0; j < N; ++j) Bi[(size_t)i * N + j] = A[(size_t)i * W + N + j];
+    // G = P Bi P
+    std::vector<double> rm(N, 0.0), cm(N, 0.0);
+    double tm = 0.0;
+    for (int i = 0; i < N; ++i)
+        for (int j = 0; j < N; ++j) {
+            rm[i] += Bi[(size_t)i * N + j] / N;
+            cm[j] += Bi[(size_t)i * N + j] / N;
+        }
+    for (int i = 0; i < N; ++i) tm += rm[i] / N;
+    G.assign((size_t)N * N, 0.0);
+    for (int i = 0; i < N; ++i)
+        for (int j = 0; j < N; ++j) G[(size_t)i * N + j] = Bi[(size_t)i * N + j] - rm[i] - cm[j] + tm;
+    return true;
 }
 
 // Carves a context's fields out of one block of device memory; with a null
@@ -1055,7 +1139,7 @@ mg_status setup_var(mg_ctx* c, int source, const void* field, const SetupMem& sm
         }
     }
     const Level& Lc = c->lev.back();
-    HIPCHK(c, launch_dense_inverse(Lc.n, Lc.ih2, sm.c64[levels - 1], c->G, sm.dense, bad + 16, s));
+    HIPCHK(c, launch_dense_inverse(Lc.n, Lc.ih2, sm.c64[levels - 1], c->G, sm.dense, bad + 16, bad + 17, s));
     static_assert(16 + kSetupSlots <= kHostDoubles && sizeof(u64) == sizeof(double), "the slots fit the host mirror");
     u64* host = reinterpret_cast<u64*>(c->hscal + 16);
     HIPCHK(c, hipMemcpyAsync(host, c->slots, kSetupSlots * sizeof(u64), hipMemcpyDeviceToHost, s));
@@ -1069,8 +1153,16 @@ mg_status setup_var(mg_ctx* c, int source, const void* field, const SetupMem& sm
                               " with a folded mesh (non-finite or non-positive diagonal coefficients)"
                         : cells + "with non-finite or non-positive diagonal coefficients");
     }
-    if (host[32] != 0)
-        return fail(c, MG_ERR_INVALID_COEFF, "coarsest operator is singular beyond its constant null space");
+    if (host[32] != 0 || host[33] != 0) {  // not definite (coefficients that are not): invert with pivoting
+        std::vector<double> C(6 * Lc.N), M, G;
+        HIPCHK(c, hipMemcpyAsync(C.data(), sm.c64[levels - 1], C.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+        HIPCHK(c, hipStreamSynchronize(s));
+        assemble_dense(Lc.n, Lc.ih2, C, M);
+        if (!pseudo_inverse((int)Lc.N, M, G))
+            return fail(c, MG_ERR_INVALID_COEFF, "coarsest operator is singular beyond its constant null space");
+        HIPCHK(c, hipMemcpyAsync(c->G, G.data(), G.size() * sizeof(double), hipMemcpyHostToDevice, s));
+        HIPCHK(c, hipStreamSynchronize(s));
+    }
     for (int l = 0; l + 1 < levels; ++l) std::memcpy(&c->lev[l].lmax, &host[l], sizeof(double));
     // levels of at most 16^3 points run in one kernel (coarsest 8^3 or 4^3)
     const int steps = p.smoother == MG_JACOBI ? p.jacobi_sweeps : p.cheb_degree;

@@ -35,9 +35,13 @@ hipError_t launch_geometry_fields(int n, double ih2, const double* psi, double* 
                                   hipStream_t s);
 
 // Zero-mean pseudo-inverse G of the 19-point operator on the coarsest level
-// (n = 4 or 8, N = n^3).  work: 2 N^2 + 2 N doubles.  Adds the number of
-// values of G that are not finite to *bad.
-hipError_t launch_dense_inverse(int n, double ih2, const double* C, double* G, double* work, u64* bad, hipStream_t s);
+// (n = 4 or 8, N = n^3), by an elimination without pivoting: right where the
+// operator is negative semidefinite, as it is for positive definite C.  work:
+// 2 N^2 + 2 N doubles.  Adds the number of values of G that are not finite to
+// *bad, and to *indefinite the number of steps that met a pivot which is not
+// negative; where either is not zero, G is to be formed with pivoting.
+hipError_t launch_dense_inverse(int n, double ih2, const double* C, double* G, double* work, u64* bad,
+                                u64* indefinite, hipStream_t s);
 inline size_t dense_work(int n) {
     const size_t N = (size_t)n * n * n;
     return 2 * N * N + 2 * N;

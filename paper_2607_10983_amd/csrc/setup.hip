@@ -7,8 +7,9 @@
 // fields to the next level (in double, with the float copy of a mixed
 // hierarchy written beside it).  Counts and bounds go to integer slots by
 // atomics (order-independent), so the host reads all levels' results once, at
-// the end, instead of waiting per level.  The coarsest dense inverse, which
-// the host computed, is a blocked Gauss-Jordan elimination in a few launches.
+// the end, instead of waiting per level.  The coarsest dense inverse of a
+// definite operator, which the host computed, is a blocked Gauss-Jordan
+// elimination in a few launches.
 // Creating a 64^3 context takes 0.17 ms with a 4^3 coarsest level and 0.6 ms
 // with 8^3; a 256^3 step (geometry in both precisions 283 us, 4.7 TB/s; bounds
 // 211 us in double, 3.8 TB/s) 0.7 ms.
@@ -436,8 +437,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_geometry_row(int n, double i
 }
 
 // ---- coarsest dense inverse -----------------------------------------------------------
-// Row i of A = M - (s / N) 1 1^T, s the mean of |diag M|: symmetric negative
-// definite, so the elimination below needs no pivoting.  One block per row.
+// Row i of A = M - (s / N) 1 1^T, s the mean of |diag M|.  One block per row.
 __global__ __launch_bounds__(kThreads) void k_dense_assemble(int n, double ih2, const double* __restrict__ C,
                                                              double* __restrict__ A) {
     __shared__ double sh[kThreads];
@@ -475,6 +475,12 @@ __global__ __launch_bounds__(kThreads) void k_dense_assemble(int n, double ih2, 
 // tile.  P is eliminated by one wave with a column of A_KK per lane in
 // registers; the pivot column comes by scalar broadcasts.  A step takes 30 us
 // (bound by the serial pivots), two for 4^3 and 16 for 8^3.
+// There is no pivoting: A is negative definite where C is positive definite,
+// and then none is needed.  The coefficients are only checked for positive
+// diagonal components, so the premise is checked here.  The pivots of a
+// symmetric matrix have the signs of its eigenvalues: a step that meets one
+// that is not negative counts itself in *indefinite, and the caller inverts
+// such a matrix with pivoting.
 constexpr int kB = 32, kT = 64;
 __device__ __forceinline__ double lane_bcast(double v, int lane) {
     v2i h = __builtin_bit_cast(v2i, v);
@@ -483,7 +489,7 @@ __device__ __forceinline__ double lane_bcast(double v, int lane) {
     return __builtin_bit_cast(double, h);
 }
 __global__ __launch_bounds__(kThreads) void k_dense_step(int N, int k, const double* __restrict__ in,
-                                                         double* __restrict__ out) {
+                                                         double* __restrict__ out, u64* indefinite) {
     __shared__ double P[kB][kB + 1], L[kT][kB + 1], U[kB][kT + 1], W[kB][kT + 1];
     const int t = threadIdx.x, k0 = k * kB, I = blockIdx.y * kT, J = blockIdx.x * kT;
     for (int e = t; e < kT * kB; e += kThreads) L[e / kB][e % kB] = in[(size_t)(I + e / kB) * N + k0 + e % kB];
@@ -496,14 +502,17 @@ __global__ __launch_bounds__(kThreads) void k_dense_step(int N, int k, const dou
         // The pivot row is always a[0]: every update moves its row down by one,
         // so after kB pivots the rows are back in order and the loop needs no
         // unrolling.
-        double inv = 1.0 / lane_bcast(a[0], 0);
+        double pivot = lane_bcast(a[0], 0), inv = 1.0 / pivot;
+        bool negative = true;
 #pragma unroll 1
         for (int p = 0; p < kB; ++p) {
             const bool own = j == p;
+            negative = negative && pivot < 0.0;
             const double r = own ? inv : a[0] * inv;
             a[0] = (own ? 0.0 : a[1]) - lane_bcast(a[1], p) * r;
             // the next pivot's reciprocal, beside the other rows' updates
-            inv = 1.0 / lane_bcast(a[0], (p + 1) & (kB - 1));
+            pivot = lane_bcast(a[0], (p + 1) & (kB - 1));
+            inv = 1.0 / pivot;
 #pragma unroll
             for (int i = 2; i < kB; ++i) {
                 const double f = lane_bcast(a[i], p);
@@ -515,6 +524,7 @@ __global__ __launch_bounds__(kThreads) void k_dense_step(int N, int k, const dou
 #pragma unroll
             for (int i = 0; i < kB; ++i) P[i][j] = a[i];
         }
+        if (t == 0 && !negative && blockIdx.x + blockIdx.y == 0) atomicAdd(indefinite, (u64)1);
     }
     __syncthreads();
     {   // W = P U, or P itself in the diagonal block's columns: 8 columns per thread
@@ -702,7 +712,8 @@ hipError_t launch_geometry_fields(int n, double ih2, const double* psi, double* 
     return hipGetLastError();
 }
 
-hipError_t launch_dense_inverse(int n, double ih2, const double* C, double* G, double* work, u64* bad, hipStream_t s) {
+hipError_t launch_dense_inverse(int n, double ih2, const double* C, double* G, double* work, u64* bad,
+                                u64* indefinite, hipStream_t s) {
     const int N = n * n * n;
     if (N % kT != 0) return hipErrorInvalidValue;
     double* a = work;
@@ -711,7 +722,8 @@ hipError_t launch_dense_inverse(int n, double ih2, const double* C, double* G, d
     double* cm = rm + N;
     hipLaunchKernelGGL(k_dense_assemble, dim3(N), dim3(kThreads), 0, s, n, ih2, C, a);
     for (int k = 0; k < N / kB; ++k) {
-        hipLaunchKernelGGL(k_dense_step, dim3(N / kT, N / kT), dim3(kThreads), 0, s, N, k, (const double*)a, b);
+        hipLaunchKernelGGL(k_dense_step, dim3(N / kT, N / kT), dim3(kThreads), 0, s, N, k, (const double*)a, b,
+                           indefinite);
         double* q = a;
         a = b;
         b = q;
