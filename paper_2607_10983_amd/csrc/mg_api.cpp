@@ -1164,12 +1164,12 @@ mg_status setup_var(mg_ctx* c, int source, const void* field, const SetupMem& sm
         HIPCHK(c, hipStreamSynchronize(s));
     }
     for (int l = 0; l + 1 < levels; ++l) std::memcpy(&c->lev[l].lmax, &host[l], sizeof(double));
-    // levels of at most 16^3 points run in one kernel (coarsest 8^3 or 4^3)
+    // levels of at most 16^3 points run in one kernel (coarsest 4^3, or 8^3 with enough steps)
     const int steps = p.smoother == MG_JACOBI ? p.jacobi_sweeps : p.cheb_degree;
     if (c->use_tail && steps <= kTailMaxSteps) {
         int l0 = levels - 1;
         while (l0 > 0 && c->lev[l0 - 1].n <= 16) --l0;
-        if (var_tail_applies(c->lev[l0].n, Lc.n, levels - l0)) c->tail_start = l0;
+        if (var_tail_applies(c->lev[l0].n, Lc.n, levels - l0, steps)) c->tail_start = l0;
     }
     return MG_OK;
 }
