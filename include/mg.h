@@ -277,8 +277,8 @@ mg_status mg_geometry_bwd(int n, double h, const double* psi, const double* Cbar
  * bits.  Where psibar overlaps an input its temporary is a library-owned
  * device array of MG_NOALLOC_SCRATCH_BYTES per GPU (allocated when the
  * library's code is loaded on that GPU, held until the process ends), which
- * holds n <= 128; a larger psibar must not overlap.  n <= MG_NOALLOC_MAX_N,
- * else MG_ERR_INVALID.  Calls no hipMalloc, hipFree or allocating routine and
+ * holds n <= 128; a larger psibar that overlaps gives MG_ERR_INVALID, as does
+ * n > MG_NOALLOC_MAX_N.  Calls no hipMalloc, hipFree or allocating routine and
  * does not synchronise (stream-ordered).  Overlapping results of calls that
  * run at the same time on one GPU (different streams or threads) share the
  * array and must be ordered by the caller. */

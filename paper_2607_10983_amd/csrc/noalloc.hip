@@ -52,9 +52,9 @@ extern "C" mg_status mg_geometry_bwd_noalloc(int n, double h, const double* psi,
     const double ih2 = 1.0 / (h * h);
     const size_t N = (size_t)n * n * n;
     hipStream_t s = (hipStream_t)stream;
-    // (an overlapping result of more points than the array holds is undefined)
-    if (N > kScratchDoubles || !geometry_bwd_overlaps(N, psi, Cbar, sqrtgbar, psibar))
+    if (!geometry_bwd_overlaps(N, psi, Cbar, sqrtgbar, psibar))
         return launch_geometry_bwd(n, ih2, psi, Cbar, sqrtgbar, psibar, s) == hipSuccess ? MG_OK : MG_ERR_HIP;
+    if (N > kScratchDoubles) return MG_ERR_INVALID;  // it would overwrite what other blocks still read
     double* tmp = nullptr;
     if (scratch_of_current_device(&tmp) != hipSuccess) {
         (void)hipGetLastError();
