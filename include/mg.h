@@ -177,7 +177,8 @@ mg_status mg_workspace_bytes(const mg_params* p, int source, size_t* keep_bytes,
 mg_status mg_create_in(const mg_params* p, int source, const void* field, void* keep, size_t keep_bytes,
                        void* setup, size_t setup_bytes, void* stream, mg_ctx** out);
 
-/* Free everything the context owns.  NULL is accepted. */
+/* Free everything the context owns, after its work on every stream it was
+ * given has finished.  NULL is accepted. */
 mg_status mg_destroy(mg_ctx* ctx);
 
 /* Order all later work of the context on stream (hipStream_t, may be NULL). */

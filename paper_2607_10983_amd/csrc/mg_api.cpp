@@ -63,6 +63,8 @@ constexpr int kSetupSlots = 34;
 struct mg_ctx {
     mg_params p{};
     hipStream_t stream = nullptr;
+    bool other_streams = false;  // work may be left on a stream it had before
+    int device = 0;
     bool var = false;
     bool inner_double = true;   // inner V-cycle in double (MG_FP64) or float
     std::vector<Level> lev;
@@ -1010,8 +1012,15 @@ mg_status mg_validate_params(const mg_params* p) {
 
 mg_status mg_destroy(mg_ctx* c) {
     if (!c) return MG_OK;
-    if (c->stream) (void)hipStreamSynchronize(c->stream);
-    else (void)hipDeviceSynchronize();
+    if (c->stream && !c->other_streams) {
+        (void)hipStreamSynchronize(c->stream);
+    } else {  // the earlier streams may be gone by now: wait for the device
+        int dev = c->device;
+        (void)hipGetDevice(&dev);
+        if (dev != c->device) (void)hipSetDevice(c->device);
+        (void)hipDeviceSynchronize();
+        if (dev != c->device) (void)hipSetDevice(dev);
+    }
     dfree(c->mem);
     if (c->hscal) host_slot_back(c->hscal);
     dfree(c->scratch);
@@ -1255,6 +1264,7 @@ mg_status create(const mg_params* p, int source, const void* field, void* keep, 
     if (!c) return MG_ERR_NOMEM;
     c->p = *p;
     c->stream = (hipStream_t)stream;
+    (void)hipGetDevice(&c->device);
     mg_status st;
     try {
         st = create_impl(c, source, field, keep, keep_bytes, setup, setup_bytes);
@@ -1324,6 +1334,7 @@ mg_status mg_create_in(const mg_params* p, int source, const void* field, void* 
 
 mg_status mg_set_stream(mg_ctx* c, void* stream) {
     if (!c) return MG_ERR_INVALID;
+    if (c->stream != (hipStream_t)stream) c->other_streams = true;
     c->stream = (hipStream_t)stream;
     return MG_OK;
 }
