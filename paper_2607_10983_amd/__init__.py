@@ -161,7 +161,8 @@ class Multigrid:
 
     def _sync_stream(self):
         stream = _torch().cuda.current_stream()
-        if stream != self._stream:  # the allocator must not hand the block out while this stream uses it
+        # the allocator must not hand the block out while another stream uses it (a closed context has none)
+        if stream != self._stream and self._keep is not None:
             self._keep.record_stream(stream)
         _lib.load().mg_set_stream(self._ctx, ctypes.c_void_p(stream.cuda_stream))
 
