@@ -166,6 +166,17 @@ class Multigrid:
             self._keep.record_stream(stream)
         _lib.load().mg_set_stream(self._ctx, ctypes.c_void_p(stream.cuda_stream))
 
+    def _call(self, fname, *args):
+        """An entry point that may allocate in the context.  The blocks of closed
+        contexts stay with torch's allocator, where the library's own
+        allocations do not find them: they are given back before one fails."""
+        fn = getattr(_lib.load(), fname)
+        st = fn(self._ctx, *args)
+        if st == _lib.MG_ERR_NOMEM:
+            _torch().cuda.empty_cache()
+            st = fn(self._ctx, *args)
+        return st
+
     # ---------------------------------------------------------------- solves
     def solve(self, b, phi0=None, tol: float = 1e-10, max_cycles: int = 50, history: bool = True,
               raise_on_error: bool = True, out=None) -> Tuple[object, SolveInfo]:
@@ -201,14 +212,13 @@ class Multigrid:
         return lam, self._run("mg_solve_adjoint", lam, phibar, tol, max_cycles, history, raise_on_error)
 
     def _run(self, fname, x, rhs, tol, max_cycles, history, raise_on_error):
-        lib = _lib.load()
         self._sync_stream()
         cap = max_cycles + 1 if history else 0
         hist = (ctypes.c_double * max(cap, 1))()
         info = _lib.MgSolveInfo()
         info.history = ctypes.cast(hist, ctypes.POINTER(ctypes.c_double)) if history else None
         info.history_cap = cap
-        st = getattr(lib, fname)(self._ctx, _ptr(x), _ptr(rhs), float(tol), int(max_cycles), ctypes.byref(info))
+        st = self._call(fname, _ptr(x), _ptr(rhs), float(tol), int(max_cycles), ctypes.byref(info))
         res = SolveInfo(info.cycles, info.rel_res0, info.rel_res,
                         [hist[i] for i in range(min(info.cycles + 1, cap))] if history else [], st)
         if st not in (_lib.MG_OK, _lib.MG_ERR_NOT_CONVERGED) or (raise_on_error and st != _lib.MG_OK):
@@ -298,7 +308,7 @@ class Multigrid:
         _check_field(b, self._level_n(level), torch.float64, "b")
         x = x.clone()
         self._sync_stream()
-        st = _lib.load().mg_smooth(self._ctx, level, _ptr(x), _ptr(b))
+        st = self._call("mg_smooth", level, _ptr(x), _ptr(b))
         if st != _lib.MG_OK:
             raise self._err(st, "mg_smooth")
         return x
@@ -311,7 +321,7 @@ class Multigrid:
             _check_field(x, nl, torch.float64, "x")
         out = torch.empty((nl // 2,) * 3, dtype=torch.float64, device=b.device)
         self._sync_stream()
-        st = _lib.load().mg_residual_restrict(self._ctx, level, _ptr(x) if x is not None else None, _ptr(b), _ptr(out))
+        st = self._call("mg_residual_restrict", level, _ptr(x) if x is not None else None, _ptr(b), _ptr(out))
         if st != _lib.MG_OK:
             raise self._err(st, "mg_residual_restrict")
         return out
