@@ -13,13 +13,13 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
 
 #include "flat_row.h"
 #include "geometry_bwd.h"
+#include "host_slots.h"
 #include "kernels.h"
 #include "pcg_row.h"
 #include "setup.h"
@@ -309,33 +309,16 @@ struct Arena {
     double* doubles(size_t count) { return (double*)take(count * sizeof(double)); }
 };
 
-// Pinned host mirrors, kHostDoubles each, handed out in pages that are kept and
-// reused: a pinned allocation costs more than a small solve.  Portable, so a
-// slot serves a context on any device.
-constexpr size_t kHostDoubles = 128, kPageSlots = 8;
-std::mutex g_host_mutex;
-std::vector<double*> g_host_free;
-hipError_t host_slot(double** out) {
-    std::lock_guard<std::mutex> lock(g_host_mutex);
-    if (g_host_free.empty()) {
-        g_host_free.reserve(kPageSlots);
-        double* page = nullptr;
-        // coherent: the finalize kernels write the outer sums into it directly
-        const hipError_t e = hipHostMalloc((void**)&page, kPageSlots * kHostDoubles * sizeof(double),
-                                           hipHostMallocCoherent | hipHostMallocPortable);
-        if (e != hipSuccess) return e;
-        for (size_t k = 0; k < kPageSlots; ++k) g_host_free.push_back(page + k * kHostDoubles);
-    }
-    *out = g_host_free.back();
-    g_host_free.pop_back();
-    return hipSuccess;
-}
-void host_slot_back(double* p) {
-    std::lock_guard<std::mutex> lock(g_host_mutex);
-    try {
-        g_host_free.push_back(p);
-    } catch (...) {  // no room to remember it: the slot is lost until the process ends
-    }
+// The contexts' pinned host mirrors.  Portable, so a slot serves a context on
+// any device; coherent: the finalize kernels write the outer sums into it
+// directly.  Never destroyed: contexts may be, after the library's statics.
+HostSlots& host_slots() {
+    static HostSlots* slots = new HostSlots(
+        [](double** page, size_t bytes) {
+            return (int)hipHostMalloc((void**)page, bytes, hipHostMallocCoherent | hipHostMallocPortable);
+        },
+        [](double* page) { (void)hipHostFree(page); });
+    return *slots;
 }
 
 template <typename T>
@@ -1022,7 +1005,7 @@ mg_status mg_destroy(mg_ctx* c) {
         if (dev != c->device) (void)hipSetDevice(dev);
     }
     dfree(c->mem);
-    if (c->hscal) host_slot_back(c->hscal);
+    if (c->hscal) host_slots().back(c->hscal);
     dfree(c->scratch);
     dfree(c->pcg_r);
     dfree(c->pcg_p[0]);
@@ -1240,7 +1223,7 @@ mg_status create_impl(mg_ctx* c, int source, const void* field, void* keep, size
     }
     Arena A{(char*)keep}, B{(char*)setup};
     layout(c, source, A, B, sm);
-    const hipError_t e = host_slot(&c->hscal);
+    const hipError_t e = (hipError_t)host_slots().take(&c->hscal);
     if (e != hipSuccess) {
         c->hscal = nullptr;
         st = fail(c, MG_ERR_HIP, std::string("pinned host memory: ") + hipGetErrorString(e));
