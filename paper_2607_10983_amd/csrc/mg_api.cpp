@@ -91,7 +91,7 @@ struct mg_ctx {
     int x1_buf = 0;             // ... into this level-0 iterate buffer
     // The coarse sub-cycle (levels 1 .. coarsest) touches only context-owned
     // buffers with fixed arguments, so it can be captured once into a HIP graph
-    // and replayed with one launch per V-cycle (MG_GRAPH set at creation).
+    // and replayed with one launch per V-cycle (MG_OPT_GRAPH).
     bool use_graph = false;
     bool capturing = false;
     hipStream_t cap_stream = nullptr;
@@ -371,8 +371,9 @@ inline int other(int cur) { return cur == 0 ? 1 : 0; }
 inline bool x1_fusable(const mg_ctx* c) { return c->tail_start != 0 && c->lev.size() > 1; }
 
 // Level l (not the coarsest, not run by the tail kernel) is visited by the
-// fused visit kernels: float hierarchy, seven-point operator, 32^3 or 64^3
-// points; pre (post) selects the visit before (after) the coarse correction.
+// fused visit kernels: seven-point operator, 32^3 points or, in a float
+// hierarchy, 64^3; pre (post) selects the visit before (after) the coarse
+// correction.
 inline bool visit_level(const mg_ctx* c, int l, bool pre) {
     if (!(c->use_visits && !c->var && c->p.smoother == MG_CHEBYSHEV && l + 1 < (int)c->lev.size() &&
           l != c->tail_start))
@@ -669,25 +670,20 @@ mg_status tail_cycle(mg_ctx* c, int l0) {
     a.sched.cheb = cheb ? 1 : 0;
     a.sched.steps = (int)c->lev[l0].a.size();
     for (int k = 0; k < a.nlev; ++k) {
-        Level& Lv = c->lev[l0 + k];
+        const Level& Lv = c->lev[l0 + k];
         a.n[k] = Lv.n;
-        int lg = 0;
-        while ((1 << lg) < Lv.n) ++lg;
-        a.lg[k] = lg;
         a.ih2[k] = Lv.ih2;
-        a.x0[k] = (T*)Lv.x[0];
-        a.x1[k] = (T*)Lv.x[1];
-        a.b[k] = (T*)Lv.b;
         for (int j = 0; j < a.sched.steps; ++j) {
             a.sched.a[k][j] = Lv.a[j];
             a.sched.c[k][j] = Lv.c[j];
         }
     }
+    a.b = (const T*)c->lev[l0].b;
+    a.x = (T*)c->lev[l0].x[0];
     a.Q = c->Q;
     a.lam1 = c->lam1;
     a.sums = take_sums(c);
     HIPCHK(c, launch_tail<T>(a, c->stream));
-    // the tail writes the first tail level's result to that level's buffer x0
     c->lev[l0].cur = 0;
     return MG_OK;
 }

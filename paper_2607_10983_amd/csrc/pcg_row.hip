@@ -31,10 +31,8 @@ namespace mg {
 namespace {
 
 constexpr int kWaves = 8;      // rows of a block
-#ifndef MAXVEC
-#define MAXVEC 4
-#endif
-constexpr int kMaxVec = MAXVEC;     // 2 KB of doubles per row tile
+constexpr int kMaxVec = 4;     // 2 KB of doubles per row tile
+static_assert(64 * kMaxVec <= 256, "a tile fits the shortest row that is split into tiles");
 constexpr int kMinPlanes = 8;  // shortest chunk
 constexpr int kTargetBlocks = 1024;
 

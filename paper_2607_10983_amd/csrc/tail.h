@@ -18,17 +18,13 @@ struct TailSchedule {
     double c[kTailMaxLevels][kTailMaxSteps];
 };
 
-// Only x0[0] and b[0] (the first tail level) are accessed in global memory:
-// the tail reads b[0] and leaves the V-cycle result in x0[0].
 template <typename T>
 struct TailArgs {
     int nlev;                      // levels in the tail, the last one is the coarsest
     int n[kTailMaxLevels];
-    int lg[kTailMaxLevels];
     double ih2[kTailMaxLevels];
-    T* x0[kTailMaxLevels];
-    T* x1[kTailMaxLevels];
-    T* b[kTailMaxLevels];
+    const T* b;                    // right-hand side of the first tail level
+    T* x;                          // its V-cycle result
     TailSchedule sched;
     const double* Q;               // coarsest separable basis (nc x nc)
     const double* lam1;            // its 1-D eigenvalues

@@ -80,7 +80,6 @@ struct Shared {
 // the thread's share of a level: the 16^3 level
 template <typename T>
 struct Seg {
-    static constexpr int K = 4;
     T x[4], b[4];
 };
 
@@ -366,9 +365,9 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<T> A) {
     T x8 = T(0), b8 = T(0);
     int w16 = 0, w8 = 0;
     if constexpr (HAS16) {
-        ldrow<T, 4>(u.b, A.b[0] + 4 * i);
+        ldrow<T, 4>(u.b, A.b + 4 * i);
     } else {
-        if (i < 512) b8 = A.b[0][i];
+        if (i < 512) b8 = A.b[i];
     }
     if (i < CST * CST) S.q[i] = A.Q[i];
     if (i < CST) S.lam[i] = A.lam1[i];
@@ -389,7 +388,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<T> A) {
             if (i < 512) e8[i] = x8;
             __syncthreads();
         } else {
-            if (i < 512) A.x0[0][i] = x8;
+            if (i < 512) A.x[i] = x8;
         }
     } else {
         if (i < 512) S.g[1][i] = b8;
@@ -399,7 +398,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<T> A) {
     if constexpr (HAS16) {
         prolong16<T>(u.x, e8);
         smooth16<T>(A, S, 0, u, w16, false);
-        strow<T, 4>(A.x0[0] + 4 * i, u.x);
+        strow<T, 4>(A.x + 4 * i, u.x);
     }
 }
 
