@@ -9,7 +9,10 @@ potential (t = 0 from zero), 7 levels (coarsest 4^3), Chebyshev degree 3, in
 mixed precision (float V-cycles, double residual/update/coarsest solve).
 All inputs are resident in HBM before timing starts.
 
-The JSON line reports V-cycle throughput of the mixed path (value), the same
+The JSON line on standard output holds the headline and the main figures of
+every leg in at most LINE_MAX characters; all of it goes to standard error as
+one more JSON line, marked "[bench] details", just before.  Reported are the
+V-cycle throughput of the mixed path (value), the same
 sequence in plain float64 (time-to-tolerance ratio), the roofline of the
 dominant kernel of the step (the fine-level kernel kind with the largest
 share of the step's time; in-dispatch HIP events around each launch,
@@ -36,6 +39,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "V-cycle Mpts/s + HBM GB/s; time to rel. residual 1e-10, mixed vs FP64"
 HBM_PEAK_GBPS = 8000.0
+LINE_MAX = 6000  # a caller that keeps the last 8 KB of the output has the line whole
 
 # Measured HBM bytes per launch of the fine-level kernels, per workload
 # (n, degree; mixed precision) and kernel kind: rocprofv3 FETCH_SIZE and
@@ -585,6 +589,41 @@ def cpu_leg(src_np, n, levels, deg, phi_mixed, phi_fp32, fp32_info, c2_cycles, c
     return out
 
 
+LEG_FIGURES = {
+    "sweep": ("cycles", "time_to_tol_ms", "cycle_frac"),
+    "b512": ("ms_per_cycle", "cycle_GBps", "cycle_frac"),
+    "moving_mesh": ("cycles", "time_to_tol_ms", "forward_ms", "forward_backward_ms"),
+    "predictors": ("total_cycles", "ms_per_sequence"),
+    "accel": ("ms", "GBps"),
+}
+
+
+def figures(leg, names):
+    """The named figures of a leg, its structure kept."""
+    out = {}
+    for k, v in leg.items():
+        if isinstance(v, dict):
+            v = figures(v, names)
+            if v:
+                out[k] = v
+        elif k in names:
+            out[k] = v
+    return out
+
+
+def headline(full):
+    """The line for standard output: all of the result but the legs, of those
+    the main figures, and of the legs as many as fit."""
+    line = {k: v for k, v in full.items() if k not in LEG_FIGURES}
+    line["legs"] = {}
+    for k, names in LEG_FIGURES.items():
+        if full.get(k):
+            line["legs"][k] = figures(full[k], names)
+            if len(json.dumps(line)) > LINE_MAX:
+                del line["legs"][k]
+    return line
+
+
 def timed(fn, steps, torch):
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -772,7 +811,8 @@ def main():
         "accel": accel,
         "cpu_baseline": cpu,
     }
-    print(json.dumps(result), flush=True)
+    print("[bench] details " + json.dumps(result), file=sys.stderr, flush=True)
+    print(json.dumps(headline(result)), flush=True)
 
 
 if __name__ == "__main__":
