@@ -124,10 +124,11 @@ __device__ __forceinline__ void xshifts(const double (&u)[VEC], const double (&h
 // planes, one barrier per plane.
 constexpr int kAccelRows = 8;
 template <typename TO, int VEC, bool MULTI>
-__global__ __launch_bounds__(64 * kAccelRows) void k_accel_lds(int n, double i12h, const double* __restrict__ phi,
+__global__ __launch_bounds__(64 * kAccelRows) void k_accel_lds(int side, double i12h, const double* __restrict__ phi,
                                                                double scale, TO* __restrict__ a, int nz, int per) {
     constexpr int W = kAccelRows, NS = 64 * VEC;
     __shared__ double rows[2][W + 4][NS];
+    const int n = MULTI ? side : NS;  // a compile-time size where a segment is a row
     const int segs = MULTI ? n / NS : 1, m = n - 1;
     const size_t N = (size_t)n * n * n;
     const int lb = xcd_logical(blockIdx.x, gridDim.x);
@@ -217,11 +218,12 @@ __device__ __forceinline__ void xshift1(const double (&u)[VEC], double h, int la
 
 // Curvilinear mesh.
 template <typename TO, int VEC, bool MULTI>
-__global__ __launch_bounds__(64 * kAccelWaves) void k_accel_row(int n, double ih2, double i12h,
+__global__ __launch_bounds__(64 * kAccelWaves) void k_accel_row(int side, double ih2, double i12h,
                                                                 const double* __restrict__ phi,
                                                                 const double* __restrict__ psi, double scale,
                                                                 TO* __restrict__ a, int nz, int per) {
     constexpr int NS = 64 * VEC;
+    const int n = MULTI ? side : NS;
     const int segs = MULTI ? n / NS : 1, m = n - 1;
     const size_t N = (size_t)n * n * n;
     const int lb = xcd_logical(blockIdx.x, gridDim.x);
@@ -321,12 +323,15 @@ hipError_t launch_accel(int n, double h, const double* phi, const double* psi, d
                         hipStream_t s) {
     const double ih2 = 1.0 / (h * h), i12h = 1.0 / (12.0 * h);
     if (n >= 64) {
-        // segments of VEC = min(n / 64, 4) values per lane; z chunks of at least
-        // 8 planes: two LDS blocks of eight rows per CU, or about 1024 blocks of four
+        // segments of VEC = min(n / 64, 4) values per lane; z chunks that give two
+        // LDS blocks of eight rows per CU, or about 1024 blocks of four in chunks of
+        // at least 8 planes.  The LDS blocks go down to 2 planes: with at least 8
+        // the uniform 64^3 readout took 7.0 us in double and 6.2 in float against 4.5
+        // and 3.9, 128^3 (4 planes) in float 9.8 against 9.0.
         const int vec = n / 64 < 4 ? n / 64 : 4, rows = psi ? kAccelWaves : kAccelRows;
         const int per = n / (64 * vec) * n / rows;
         int nz = n;
-        while (nz > 8 && (long)per * (n / nz) < (psi ? 1024 : 512)) nz >>= 1;
+        while (nz > (psi ? 8 : 2) && (long)per * (n / nz) < (psi ? 1024 : 512)) nz >>= 1;
         const dim3 grid(per * (n / nz)), block(64 * rows);
 #define MG_ACCEL(VEC, MULTI)                                                                                       \
     do {                                                                                                           \
