@@ -128,7 +128,7 @@ __global__ __launch_bounds__(64 * kAccelRows) void k_accel_lds(int side, double 
                                                                double scale, TO* __restrict__ a, int nz, int per) {
     constexpr int W = kAccelRows, NS = 64 * VEC;
     __shared__ double rows[2][W + 4][NS];
-    const int n = MULTI ? side : NS;  // a compile-time size where a segment is a row
+    const int n = MULTI ? side : NS;
     const int segs = MULTI ? n / NS : 1, m = n - 1;
     const size_t N = (size_t)n * n * n;
     const int lb = xcd_logical(blockIdx.x, gridDim.x);
@@ -223,7 +223,9 @@ __global__ __launch_bounds__(64 * kAccelWaves) void k_accel_row(int side, double
                                                                 const double* __restrict__ psi, double scale,
                                                                 TO* __restrict__ a, int nz, int per) {
     constexpr int NS = 64 * VEC;
-    const int n = MULTI ? side : NS;
+    // a compile-time size for 64^3 (8.1 -> 7.6 us in float); where a lane holds
+    // more values it cost registers (256^3 float 157 -> 192)
+    const int n = VEC > 1 ? side : NS;
     const int segs = MULTI ? n / NS : 1, m = n - 1;
     const size_t N = (size_t)n * n * n;
     const int lb = xcd_logical(blockIdx.x, gridDim.x);
