@@ -479,8 +479,8 @@ __global__ __launch_bounds__(kThreads) void k_dense_assemble(int n, double ih2, 
 // and then none is needed.  The coefficients are only checked for positive
 // diagonal components, so the premise is checked here.  The pivots of a
 // symmetric matrix have the signs of its eigenvalues: a step that meets one
-// that is not negative counts itself in *indefinite, and the caller inverts
-// such a matrix with pivoting.
+// that is positive counts itself in *indefinite, and the caller inverts such a
+// matrix with pivoting (a zero or NaN pivot leaves values that are not finite).
 constexpr int kB = 32, kT = 64;
 __device__ __forceinline__ double lane_bcast(double v, int lane) {
     v2i h = __builtin_bit_cast(v2i, v);
@@ -502,17 +502,16 @@ __global__ __launch_bounds__(kThreads) void k_dense_step(int N, int k, const dou
         // The pivot row is always a[0]: every update moves its row down by one,
         // so after kB pivots the rows are back in order and the loop needs no
         // unrolling.
-        double pivot = lane_bcast(a[0], 0), inv = 1.0 / pivot;
-        bool negative = true;
+        double inv = 1.0 / lane_bcast(a[0], 0);
+        int signs = -1;  // of the pivots, and-ed: by the scalar unit, off the serial chain
 #pragma unroll 1
         for (int p = 0; p < kB; ++p) {
             const bool own = j == p;
-            negative = negative && pivot < 0.0;
+            signs &= __builtin_amdgcn_readlane(__builtin_bit_cast(v2i, a[0]).y, p);
             const double r = own ? inv : a[0] * inv;
             a[0] = (own ? 0.0 : a[1]) - lane_bcast(a[1], p) * r;
             // the next pivot's reciprocal, beside the other rows' updates
-            pivot = lane_bcast(a[0], (p + 1) & (kB - 1));
-            inv = 1.0 / pivot;
+            inv = 1.0 / lane_bcast(a[0], (p + 1) & (kB - 1));
 #pragma unroll
             for (int i = 2; i < kB; ++i) {
                 const double f = lane_bcast(a[i], p);
@@ -524,7 +523,7 @@ __global__ __launch_bounds__(kThreads) void k_dense_step(int N, int k, const dou
 #pragma unroll
             for (int i = 0; i < kB; ++i) P[i][j] = a[i];
         }
-        if (t == 0 && !negative && blockIdx.x + blockIdx.y == 0) atomicAdd(indefinite, (u64)1);
+        if (t == 0 && signs >= 0 && blockIdx.x + blockIdx.y == 0) atomicAdd(indefinite, (u64)1);
     }
     __syncthreads();
     {   // W = P U, or P itself in the diagonal block's columns: 8 columns per thread
