@@ -1157,7 +1157,8 @@ mg_status setup_var(mg_ctx* c, int source, const void* field, const SetupMem& sm
     if (c->use_tail && steps <= kTailMaxSteps) {
         int l0 = levels - 1;
         while (l0 > 0 && c->lev[l0 - 1].n <= 16) --l0;
-        if (var_tail_applies(c->lev[l0].n, Lc.n, levels - l0, steps)) c->tail_start = l0;
+        if (var_tail_applies(c->lev[l0].n, Lc.n, levels - l0, l0, steps, c->inner_double ? sizeof(double) : sizeof(float)))
+            c->tail_start = l0;
     }
     return MG_OK;
 }

@@ -1088,7 +1088,7 @@ hipError_t launch_var_smooth_pair(int n, double ih2, const TC* C, const T* x, co
 // residual and restriction (longer rows do not leave registers for the coarse
 // rows).  Against the prolongation and the step: float 256^3 150 -> 141 us,
 // 128^3 19.3 -> 16.6, 64^3 8.7 -> 5.4; double 128^3 35.4 -> 31.4, 64^3
-// 13.0 -> 7.0 (a 64^3 moving-mesh step 1004 -> 936 us).
+// 13.0 -> 7.0 (a 64^3 moving-mesh step 1004 -> 970 us).
 bool var_pro_applies(int n, size_t elem) { return var_row_kernels_apply(n) && (size_t)n * elem <= 1024; }
 
 template <typename T, typename TC>

@@ -664,9 +664,9 @@ __global__ __launch_bounds__(tail_threads<T>()) void k_var_tail(VarTailArgs<T> A
 
 template <typename T>
 hipError_t launch_var_tail(const VarTailArgs<T>& a, hipStream_t s) {
-    if (a.nlev < 2 || a.nlev > 3 || a.sched.steps < 1 || a.sched.steps > kTailMaxSteps ||
-        !var_tail_applies(a.n[0], a.n[a.nlev - 1], a.nlev, a.sched.steps))
-        return hipErrorInvalidValue;
+    if (a.nlev < 2 || a.nlev > 3 || a.sched.steps < 1 || a.sched.steps > kTailMaxSteps) return hipErrorInvalidValue;
+    const bool dense8 = a.nlev == 2 && a.n[0] == 16 && a.n[1] == 8;
+    if (!dense8 && !(a.n[a.nlev - 1] == 4 && var_tail_dense4(a.n[0], a.nlev))) return hipErrorInvalidValue;
     const dim3 grid(a.sums.count > 0 ? 2 : 1);
     if (a.n[0] == 8) hipLaunchKernelGGL((k_var_tail<T, false, false>), grid, dim3(tail_threads<T>()), 0, s, a);
     else if (a.n[a.nlev - 1] == 4) hipLaunchKernelGGL((k_var_tail<T, true, false>), grid, dim3(tail_threads<T>()), 0, s, a);
