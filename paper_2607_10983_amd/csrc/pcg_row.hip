@@ -11,8 +11,8 @@
 //
 // 11 fields of 8 bytes per iteration in double instead of 14 with q and a
 // copy of r.  256^3 double against the passes that store q: direction 211 ->
-// 73 us (5.5 TB/s), update 168 -> 114 (5.9), dots 82 -> 88 (4.6), residual
-// with its three sums 159 + 27 -> 90.
+// 78 us (5.2 TB/s), update 168 -> 130 (5.2), dots 82 -> 95 (4.2), residual
+// with its three sums 159 + 27 -> 85.
 //
 // A block owns an x tile of 64 VEC points of kWaves consecutive rows and
 // marches a chunk of planes: a wave keeps its row of u (the field under the
