@@ -130,7 +130,9 @@ mg_status mg_validate_params(const mg_params* p);
  * Coarse-level coefficients are the componentwise full-weighting restriction
  * of the fine ones (App. B restricts the geometry to every level).  The
  * coarsest level of a variable-coefficient context may have at most 8^3
- * points (it is solved with a dense pseudo-inverse).  stream: hipStream_t or
+ * points (it is solved with a dense pseudo-inverse, formed with pivoting
+ * where coefficients that are not positive definite make the operator
+ * indefinite).  stream: hipStream_t or
  * NULL.  On success *out owns its device memory until mg_destroy.
  * Errors: MG_ERR_INVALID (parameters), MG_ERR_INVALID_COEFF (coefficients not
  * finite or a diagonal component <= 0), MG_ERR_NOMEM, MG_ERR_HIP. */
@@ -233,8 +235,9 @@ mg_status mg_cycles(mg_ctx* ctx, double* phi, const double* b, int cycles, doubl
  * info->cycles counts CG iterations (one V-cycle each), history holds the
  * recursive residuals (the true one where a restart happened) and rel_res
  * the true final residual.  b's mean is projected out first and phi's mean
- * removed at the end, as in mg_solve.  Allocates four n^3 double work fields
- * in the context on first use.  Same errors as mg_solve. */
+ * removed at the end, as in mg_solve.  Allocates two to four n^3 double work
+ * fields in the context on first use.  Same errors as mg_solve, and
+ * MG_ERR_NOMEM. */
 mg_status mg_solve_pcg(mg_ctx* ctx, double* phi, const double* b, double tol,
                        int max_iter, mg_solve_info* info);
 
